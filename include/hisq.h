@@ -236,7 +236,10 @@ int hisq_dot_noalloc(const void *x, const void *y, long long n, int prec, double
  * buffers (dst = D src on parity 1, `reps` launches each, 20 if <= 0),
  * remembers the fastest for (dims, prec) in this process -- and in the file
  * named by the environment variable HISQ_TUNE_CACHE, if set -- and uses it
- * in every later Dslash of that lattice and precision.  The plain CG's fused
+ * in every later Dslash of that lattice and precision (lattices of few
+ * 64-site tiles per parity -- at most 768 in HISQ_F64, 1280 in HISQ_F64C,
+ * HISQ_F32 and HISQ_F32C, 2600 with 16-bit links -- take one form of their
+ * own, whatever the shape).  The plain CG's fused
  * kernels take the tile order of the chosen shape; for HISQ_F64 a shape with
  * a blocked tile order is chosen only when it is more than 3 % faster than
  * the fastest plain-order shape (the blocked orders slow the CG solve down

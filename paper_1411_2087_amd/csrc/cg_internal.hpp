@@ -41,22 +41,6 @@ struct CGState {
     int pad_;
 };
 
-// Algorithmic bytes per site of the byte model of every solver's bytes_moved:
-// the 16 link matrices of one Dslash in precision `prec` (a two-row long
-// matrix is 96, 48 or 28 bytes) and one colour vector of its vector type.
-inline double link_bytes_site(int prec)
-{
-    switch (prec) {
-    case HISQ_F64: return 16 * 144.0;
-    case HISQ_F32: return 16 * 72.0;
-    case HISQ_F16S:
-    case HISQ_I16S: return 16 * 40.0;
-    case HISQ_F64C: return 8 * 144.0 + 8 * 96.0;
-    case HISQ_F32C: return 8 * 72.0 + 8 * 48.0;
-    default: return 8 * 40.0 + 8 * 28.0;  // HISQ_I16SC
-    }
-}
-inline double vec_bytes(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 48.0 : 24.0; }
 
 // Scratch of the standalone dot product: the per-workgroup partials of the
 // first stage (at most BLAS_MAX_BLOCKS workgroups, striding over the vectors)

@@ -40,6 +40,46 @@ __global__ __launch_bounds__(NT) HISQ_WAVES(W) void k_dslash(Geom g, const char 
     }
 }
 
+// The split form (SplitTerms): one tile per workgroup.  XM: y = m4 x - D src (the second half of A), else y = D src.
+template <class P, bool KEEP, bool XM>
+__global__ __launch_bounds__(SPLIT_NT) void k_dslash_split(Geom g, const char *__restrict__ fat,
+                                                           const char *__restrict__ lng,
+                                                           const typename P::cvec *__restrict__ src,
+                                                           const typename P::real *__restrict__ x,
+                                                           typename P::real *__restrict__ dst, double m4, int parity,
+                                                           const SolverFlags *flags, int gate)
+{
+    using T = SplitTerms<P, KEEP>;
+    using R = typename P::real;
+    __shared__ __align__(16) R red[SPLIT * TILE_REALS];
+    if (gate_closed(flags, gate)) return;
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    if (tile >= g.ntiles) return;
+    const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = tile * TILE + lane;
+    T terms;
+    terms.load(g, fat, lng, parity, tile, lane, h < g.Vh ? h : g.Vh - 1, q);
+    typename P::cvec f[3], l[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        f[a] = src[(size_t)terms.nf * 3 + a];
+        l[a] = src[(size_t)terms.nl * 3 + a];
+    }
+    const int i = threadIdx.x;
+    const bool own = i < min(TILE_REALS, (g.Vh - tile * TILE) * 6);
+    const size_t at = (size_t)tile * TILE_REALS + i;
+    R xv = 0;
+    if (XM && own) xv = x[at];
+    R acc[6];
+    terms.products(f, l, acc);
+    T::put(acc, q, lane, red);
+    __syncthreads();
+    if (!own) return;
+    const R s = T::result(red, i);
+    if constexpr (XM) dst[at] = fma((R)m4, xv, -s);
+    else __builtin_nontemporal_store(s, dst + at);
+}
+
 // y = m4 * x - D src on parity 0 (second half of A = 4m^2 - D_eo D_oe)
 template <class P, int NT>
 __global__ __launch_bounds__(NT) HISQ_WAVES((P::prec == HISQ_F64 || P::prec == HISQ_F64C) ? 6 : 8) void k_dslash_axmy(Geom g, const char *__restrict__ fat,
@@ -98,6 +138,46 @@ static void launch_shape(const Geom &g0, const void *fat, const void *lng, const
                        gate);
 }
 
+// Where the line lies, both sides measured in microseconds (the best launch
+// shape, split); beyond it 8 streams per tile cost DRAM efficiency:
+//            16^4       16^3 x 32   20^4        24^4        28^4
+//   tiles    512        1024        1250        2592        4802
+//   F64      19.6 13.0  25.2 27.0   32.2 35.0   69.2 70.5    127  138
+//   F64C     19.8 14.9  24.6 21.3   35.7 29.5   60.7 61.6
+//   F32      11.6  7.7  13.2 12.9   17.5 15.6   34.4 35.2   62.7 63.6
+//   F32C     11.2  7.0  12.7 11.4   18.0 13.6   28.7 29.6   54.6 56.1
+//   I16SC     9.6  5.7  10.5  8.1   14.7  9.5   20.1 17.0   36.0 34.8
+bool split_tiles(const Geom &g, int prec)
+{
+    switch (prec) {
+    case HISQ_F64: return g.ntiles <= 768;
+    case HISQ_F64C:
+    case HISQ_F32:
+    case HISQ_F32C: return g.ntiles <= 1280;
+    default: return g.ntiles <= 2600;
+    }
+}
+
+// The links of both parities against the 256 MB last-level cache.  Streaming
+// loads do not leave them there: split Dslash, streamed and through the
+// caches: FP64 16^4 (151 MB) 14.9, 13.0 us; I16SC 24^4 (180 MB) 20.3, 17.0;
+// FP32 24^4 (382 MB) 35.2, 37.8.
+bool links_stay_cached(const Geom &g, int prec) { return 2.0 * g.Vh * link_bytes_site(prec) <= 256e6; }
+
+// the split form where the lattice asks for it; false: not launched
+template <class P, bool XM>
+static bool launch_split(const Geom &g, const void *fat, const void *lng, const void *src, const void *x, void *dst,
+                         double m4, int parity, hipStream_t s, const SolverFlags *flags = nullptr,
+                         int gate = GATE_ALWAYS)
+{
+    using R = typename P::real;
+    if (!split_tiles(g, P::prec)) return false;
+    auto k = links_stay_cached(g, P::prec) ? k_dslash_split<P, true, XM> : k_dslash_split<P, false, XM>;
+    hipLaunchKernelGGL(k, dim3(xcd_grid(g.ntiles)), dim3(SPLIT_NT), 0, s, g, (const char *)fat, (const char *)lng,
+                       (const typename P::cvec *)src, (const R *)x, (R *)dst, m4, parity, flags, gate);
+    return true;
+}
+
 template <class P>
 hipError_t launch_dslash_shape(int shape, const Geom &g, const void *fat, const void *lng, const void *src, void *dst,
                                int parity, hipStream_t s, const SolverFlags *flags, int gate)
@@ -124,6 +204,7 @@ template <class P>
 hipError_t launch_dslash(const Geom &g, const void *fat, const void *lng, const void *src, void *dst, int parity,
                          hipStream_t s, const SolverFlags *flags, int gate)
 {
+    if (launch_split<P, false>(g, fat, lng, src, nullptr, dst, 0.0, parity, s, flags, gate)) return hipGetLastError();
     return launch_dslash_shape<P>(tuned_dslash_shape(g, P::prec), g, fat, lng, src, dst, parity, s, flags, gate);
 }
 
@@ -149,6 +230,7 @@ static hipError_t launch_apply_A(const Geom &g, double mass, const void *fat, co
 {
     hipError_t e = launch_dslash<P>(g, fat, lng, x, tmp, 1, s);
     if (e != hipSuccess) return e;
+    if (launch_split<P, true>(g, fat, lng, tmp, x, y, 4.0 * mass * mass, 0, s)) return hipGetLastError();
     const int nb = blocks_for(g, AXMY_NT);
     hipLaunchKernelGGL((k_dslash_axmy<P, AXMY_NT>), dim3(xcd_grid(nb)), dim3(AXMY_NT), 0, s, g,
                        (const char *)fat, (const char *)lng, (const typename P::cvec *)tmp,

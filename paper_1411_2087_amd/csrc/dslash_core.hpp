@@ -117,6 +117,97 @@ __device__ __forceinline__ void dslash_site(const Geom &g, const char *__restric
     }
 }
 
+// ------------------------------------------------------------------ small lattices: one tile per workgroup
+// With one wavefront per 64-site tile a lattice of few tiles leaves the chip
+// empty (16^4: 512 wavefronts for 1024 SIMDs) and each wavefront walks 16
+// rounds of loads, of which only one or two are in flight.  The split form
+// gives a tile to the 8 wavefronts of a workgroup: wavefront q takes the
+// one-link and the three-link term of direction q, all its loads in flight at
+// once, and the 8 partial sums meet in LDS, where they are added in the order
+// of q.  Bound by latency (launch, one round trip to memory, one barrier).
+// Microseconds per Dslash, one wavefront per tile -> split (4 and 16
+// wavefronts per tile are within 5 %, or slower):
+//   FP64   8^4 16.2 -> 3.6, 16^4 20.6 -> 13.0, 20^4 42.1 -> 35.4
+//   FP32   8^4 12.5 -> 2.9, 16^4 14.2 -> 7.7, 20^4 21.4 -> 15.6, 28^4 66.2 -> 63.6
+//   I16SC  8^4 12.7 -> 3.0, 16^4 13.7 -> 5.7, 20^4 16.5 -> 9.5, 28^4 39.0 -> 35.1
+// KEEP: link loads through the caches (links_stay_cached).
+constexpr int SPLIT = 8;
+constexpr int SPLIT_NT = SPLIT * TILE;
+constexpr int TILE_REALS = 6 * TILE;  // reals of a tile's colour vectors
+static_assert(TILE_REALS <= SPLIT_NT, "one real of the result per thread");
+
+template <class P, bool KEEP> struct SplitTerms {
+    using R = typename P::real;
+    using V = typename P::cvec;
+    R mf[18], ml[18];
+    R c;          // sign of a two-row link's third row
+    int nf, nl;   // neighbours
+    // the loads of the wavefront's links, and its neighbours' numbers
+    __device__ __forceinline__ void load(const Geom &g, const char *__restrict__ fat, const char *__restrict__ lng,
+                                         int parity, int tile, int lane, int h, int q)
+    {
+        int x, y, z, t;
+        site_coords(g, h, parity, x, y, z, t);
+        const size_t tix = (size_t)parity * g.ntiles + tile;
+        const char *lb = lng + tix * P::Long::tile_bytes;
+        nf = nbr_h(g, h, x, y, z, t, q & 3, q >= 4 ? -1 : 1);
+        nl = nbr_h(g, h, x, y, z, t, q & 3, q >= 4 ? -3 : 3);
+        P::Fat::template load_dir<KEEP>(fat + tix * P::Fat::tile_bytes, q, lane, mf);
+        if constexpr (P::Long::two_row) c = P::Long::template load_rows<KEEP>(lb, q, lane, ml);
+        else P::Long::template load_dir<KEEP>(lb, q, lane, ml);
+    }
+    // the two terms of the neighbour vectors f (one hop) and l (three hops)
+    __device__ __forceinline__ void products(const V f[3], const V l[3], R acc[6]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) acc[i] = 0;
+        cmac<P>(acc, mf, f[0], f[1], f[2]);
+        if constexpr (P::Long::two_row) cmac_two_row<P>(acc, ml, c, l[0], l[1], l[2]);
+        else cmac<P>(acc, ml, l[0], l[1], l[2]);
+    }
+    __device__ __forceinline__ static void put(const R acc[6], int q, int lane, R *red)
+    {
+        V *o = reinterpret_cast<V *>(red + q * TILE_REALS + 6 * lane);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            V v;
+            v.x = acc[2 * i];
+            v.y = acc[2 * i + 1];
+            o[i] = v;
+        }
+    }
+    // after a barrier: real i of the tile's result (site i / 6; colour and re / im i % 6)
+    __device__ __forceinline__ static R result(const R *red, int i)
+    {
+        R s = red[i];
+#pragma unroll
+        for (int q = 1; q < SPLIT; ++q) s += red[q * TILE_REALS + i];
+        return s;
+    }
+};
+// Algorithmic bytes per site of the byte model of every solver's bytes_moved:
+// the 16 link matrices of one Dslash in precision `prec` (a two-row long
+// matrix is 96, 48 or 28 bytes) and one colour vector of its vector type.
+inline double link_bytes_site(int prec)
+{
+    switch (prec) {
+    case HISQ_F64: return 16 * 144.0;
+    case HISQ_F32: return 16 * 72.0;
+    case HISQ_F16S:
+    case HISQ_I16S: return 16 * 40.0;
+    case HISQ_F64C: return 8 * 144.0 + 8 * 96.0;
+    case HISQ_F32C: return 8 * 72.0 + 8 * 48.0;
+    default: return 8 * 40.0 + 8 * 28.0;  // HISQ_I16SC
+    }
+}
+inline double vec_bytes(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 48.0 : 24.0; }
+
+// Whether a lattice takes the split form in this precision, whatever launch
+// shape is chosen for it, and whether its packed links stay in the last-level
+// cache from one launch to the next (dslash.hip).
+bool split_tiles(const Geom &g, int prec);
+bool links_stay_cached(const Geom &g, int prec);
+
 // Kernel gates read from a solver's device-resident state (NULL: always run).
 struct SolverFlags {
     int done;      // nonzero: solve finished (converged or broke down)

@@ -256,6 +256,14 @@ __device__ __forceinline__ void ntstore(float2 v, float2 *p)
     __builtin_nontemporal_store(w, reinterpret_cast<nf2 *>(p));
 }
 
+// A link load: streamed once (nontemporal), or with KEEP through the caches
+// (links that stay in L2 from one launch to the next).
+template <bool KEEP, class T> __device__ __forceinline__ T lload(const T *p)
+{
+    if constexpr (KEEP) return *p;
+    else return ntload(p);
+}
+
 // ------------------------------------------------------------------ precision traits
 // Packed link block of one (tile, direction): the 9 complex entries of the
 // 64 sites' matrices in element planes, each plane contiguous over the 64
@@ -272,16 +280,18 @@ struct PF64 {
     using Fat = PF64;
     using Long = PF64;
     static constexpr size_t tile_bytes = 8 * block_bytes;  // the 8 directions of one 64-site tile
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, real m[18])
     {
-        load(tile + (size_t)d * block_bytes, lane, m);
+        load<KEEP>(tile + (size_t)d * block_bytes, lane, m);
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load(const char *blk, int lane, double m[18])
     {
         const double2 *p = reinterpret_cast<const double2 *>(blk) + lane;
 #pragma unroll
         for (int e = 0; e < 9; ++e) {
-            double2 v = ntload(p + e * TILE);
+            double2 v = lload<KEEP>(p + e * TILE);
             m[2 * e] = v.x;
             m[2 * e + 1] = v.y;
         }
@@ -297,20 +307,22 @@ struct PF32 {
     using Fat = PF32;
     using Long = PF32;
     static constexpr size_t tile_bytes = 8 * block_bytes;  // the 8 directions of one 64-site tile
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, real m[18])
     {
-        load(tile + (size_t)d * block_bytes, lane, m);
+        load<KEEP>(tile + (size_t)d * block_bytes, lane, m);
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load(const char *blk, int lane, float m[18])
     {
         const float4 *p4 = reinterpret_cast<const float4 *>(blk) + lane;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            float4 v = ntload(p4 + q * TILE);
+            float4 v = lload<KEEP>(p4 + q * TILE);
             m[4 * q] = v.x; m[4 * q + 1] = v.y; m[4 * q + 2] = v.z; m[4 * q + 3] = v.w;
         }
         const float2 *p2 = reinterpret_cast<const float2 *>(blk + 4 * TILE * 16) + lane;
-        float2 v = ntload(p2);
+        float2 v = lload<KEEP>(p2);
         m[16] = v.x;
         m[17] = v.y;
     }
@@ -325,17 +337,19 @@ struct PF16S {
     using Fat = PF16S;
     using Long = PF16S;
     static constexpr size_t tile_bytes = 8 * block_bytes;  // the 8 directions of one 64-site tile
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, real m[18])
     {
-        load(tile + (size_t)d * block_bytes, lane, m);
+        load<KEEP>(tile + (size_t)d * block_bytes, lane, m);
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load(const char *blk, int lane, float m[18])
     {
         const uint4 *p4 = reinterpret_cast<const uint4 *>(blk) + lane;
-        uint4 a = ntload(p4);
-        uint4 b = ntload(p4 + TILE);
+        uint4 a = lload<KEEP>(p4);
+        uint4 b = lload<KEEP>(p4 + TILE);
         const uint2 *p2 = reinterpret_cast<const uint2 *>(blk + 2 * TILE * 16) + lane;
-        uint2 c = ntload(p2);
+        uint2 c = lload<KEEP>(p2);
         const float s = __uint_as_float(c.y);
         const unsigned w[9] = { a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x };
 #pragma unroll
@@ -360,17 +374,19 @@ struct PI16S {
     using Fat = PI16S;
     using Long = PI16S;
     static constexpr size_t tile_bytes = 8 * block_bytes;  // the 8 directions of one 64-site tile
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, real m[18])
     {
-        load(tile + (size_t)d * block_bytes, lane, m);
+        load<KEEP>(tile + (size_t)d * block_bytes, lane, m);
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load(const char *blk, int lane, float m[18])
     {
         const uint4 *p4 = reinterpret_cast<const uint4 *>(blk) + lane;
-        uint4 a = ntload(p4);
-        uint4 b = ntload(p4 + TILE);
+        uint4 a = lload<KEEP>(p4);
+        uint4 b = lload<KEEP>(p4 + TILE);
         const uint2 *p2 = reinterpret_cast<const uint2 *>(blk + 2 * TILE * 16) + lane;
-        uint2 c = ntload(p2);
+        uint2 c = lload<KEEP>(p2);
         const float s = __uint_as_float(c.y) * (1.0f / 32767.0f);
         const unsigned w[9] = { a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x };
 #pragma unroll
@@ -415,20 +431,22 @@ struct PF64R {
     static constexpr bool two_row = true;
     static constexpr size_t tile_bytes = 8 * block_bytes + 64;
     // rows 0 and 1 into m[0..11]; returns the sign c of the third row
+    template <bool KEEP = false>
     __device__ __forceinline__ static double load_rows(const char *tile, int d, int lane, double m[12])
     {
         const double2 *p = reinterpret_cast<const double2 *>(tile + (size_t)d * block_bytes) + lane;
 #pragma unroll
         for (int e = 0; e < 6; ++e) {
-            double2 v = ntload(p + e * TILE);
+            double2 v = lload<KEEP>(p + e * TILE);
             m[2 * e] = v.x;
             m[2 * e + 1] = v.y;
         }
         return ((sign_word(tile, block_bytes, d) >> lane) & 1ull) ? -1.0 : 1.0;
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, double m[18])
     {
-        const double c = load_rows(tile, d, lane, m);
+        const double c = load_rows<KEEP>(tile, d, lane, m);
         third_row<double>(m, c);
     }
 };
@@ -439,19 +457,21 @@ struct PF32R {
     static constexpr size_t block_bytes = 3 * TILE * 16;
     static constexpr bool two_row = true;
     static constexpr size_t tile_bytes = 8 * block_bytes + 64;
+    template <bool KEEP = false>
     __device__ __forceinline__ static float load_rows(const char *tile, int d, int lane, float m[12])
     {
         const float4 *p = reinterpret_cast<const float4 *>(tile + (size_t)d * block_bytes) + lane;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            float4 v = ntload(p + q * TILE);
+            float4 v = lload<KEEP>(p + q * TILE);
             m[4 * q] = v.x; m[4 * q + 1] = v.y; m[4 * q + 2] = v.z; m[4 * q + 3] = v.w;
         }
         return ((sign_word(tile, block_bytes, d) >> lane) & 1ull) ? -1.0f : 1.0f;
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, float m[18])
     {
-        const float c = load_rows(tile, d, lane, m);
+        const float c = load_rows<KEEP>(tile, d, lane, m);
         third_row<float>(m, c);
     }
 };
@@ -466,12 +486,13 @@ struct PI16R {
     static constexpr size_t block_bytes = TILE * 28;
     static constexpr bool two_row = true;
     static constexpr size_t tile_bytes = 8 * block_bytes + 64;
+    template <bool KEEP = false>
     __device__ __forceinline__ static float load_rows(const char *tile, int d, int lane, float m[12])
     {
         const char *blk = tile + (size_t)d * block_bytes;
-        const uint4 a = ntload(reinterpret_cast<const uint4 *>(blk) + lane);
-        const uint2 b = ntload(reinterpret_cast<const uint2 *>(blk + TILE * 16) + lane);
-        const float s = ntload(reinterpret_cast<const float *>(blk + TILE * 24) + lane) * (1.0f / 32767.0f);
+        const uint4 a = lload<KEEP>(reinterpret_cast<const uint4 *>(blk) + lane);
+        const uint2 b = lload<KEEP>(reinterpret_cast<const uint2 *>(blk + TILE * 16) + lane);
+        const float s = lload<KEEP>(reinterpret_cast<const float *>(blk + TILE * 24) + lane) * (1.0f / 32767.0f);
         const unsigned w[6] = { a.x, a.y, a.z, a.w, b.x, b.y };
 #pragma unroll
         for (int e = 0; e < 6; ++e) {
@@ -480,9 +501,10 @@ struct PI16R {
         }
         return ((sign_word(tile, block_bytes, d) >> lane) & 1ull) ? -1.0f : 1.0f;
     }
+    template <bool KEEP = false>
     __device__ __forceinline__ static void load_dir(const char *tile, int d, int lane, float m[18])
     {
-        const float c = load_rows(tile, d, lane, m);
+        const float c = load_rows<KEEP>(tile, d, lane, m);
         third_row<float>(m, c);
     }
 };

@@ -95,12 +95,21 @@ void set_tuned_choice(const char *kind, const Geom &g, int prec, int n, int v)
 }
 
 // Untuned default per precision: two terms unrolled at 5 waves per SIMD for
-// the FP64 forms, one term at 8 waves for the others.
-static int default_dslash_shape(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 10 : 0; }
+// the FP64 forms, every term in flight for FP32 links, four terms at 4 waves
+// for 16-bit ones.  Microseconds on 32x40x24x96 (one term at 8 waves, this):
+// F32 316, 298; F32C 272, 262; F16S 190, 177; I16S 189, 175; I16SC 172, 163.
+// FP64 with more workgroups of four tiles than CUs, but not twice as many,
+// takes workgroups of one tile, which level the last round (20^4: 41.5, 32.2).
+static int default_dslash_shape(const Geom &g, int prec)
+{
+    if (prec == HISQ_F64 && g.ntiles > 1024 && g.ntiles <= 1536) return 2;
+    if (prec == HISQ_F64 || prec == HISQ_F64C) return 10;
+    return (prec == HISQ_F32 || prec == HISQ_F32C) ? 3 : 4;
+}
 
 int tuned_dslash_shape(const Geom &g, int prec)
 {
-    const int def = default_dslash_shape(prec);
+    const int def = default_dslash_shape(g, prec);
     int v = tuned_choice("dslash", g, prec, 1, def);
     return (v >= 0 && v < N_DSLASH_SHAPES) ? v : def;
 }

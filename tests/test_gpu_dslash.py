@@ -212,3 +212,34 @@ def test_read_probe_reads_every_byte_once(hq):
     assert float(sink.sum()) == float(n)
     with pytest.raises(hq.HisqError):
         hq.hisq_read_probe(buf, torch.zeros(16, dtype=torch.float64, device="cuda"))
+
+
+# the last lattice of each precision's one-tile-per-workgroup form and the first beyond it, which is ragged
+@pytest.mark.parametrize("prec,tol,dims", [
+    (0, TOL_F64, (16, 16, 16, 24)), (0, TOL_F64, (14, 14, 18, 28)),       # 768, 772 tiles
+    (4, TOL_F64, (20, 16, 16, 32)), (4, TOL_F64, (18, 18, 22, 24)),       # 1280, 1337 tiles
+    (1, TOL_F32, (20, 16, 16, 32)), (1, TOL_F32, (18, 18, 22, 24)),
+    (5, TOL_F32, (20, 16, 16, 32)), (5, TOL_F32, (18, 18, 22, 24)),
+    (6, TOL_I16S, (24, 24, 24, 24)), (6, TOL_I16S, (22, 26, 22, 28))],    # 2592, 2753 tiles
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_dslash_and_A_at_the_split_line(hq, prec, tol, dims):
+    import torch
+    fat, lng = fields(dims, 1500 + prec)
+    mass = 0.07
+    src = synth.source(dims, 3100)
+    if prec not in (0, 4):
+        src = src.astype(np.complex64).astype(np.complex128)
+    for parity in (0, 1):
+        got = _dslash_gpu(hq, dims, fat, lng, src, parity, prec)
+        err = oracle.componentwise_error(got, oracle.dslash(dims, fat, lng, src, parity),
+                                         oracle.dslash_scale(dims, fat, lng, src, parity))
+        say(f"dslash {dims} prec={prec} parity={parity}: componentwise {err:.3e}")
+        assert err <= tol
+    L = hq.fields.Links.pack(fat, lng, dims, prec)
+    s = torch.from_numpy(src).to(hq.fields.VEC_DTYPE[prec]).cuda()
+    y, t = torch.full_like(s, float("nan")), torch.empty_like(s)
+    hq.hisq_apply_A(mass, L.fat, L.lng, s, y, t, dims, prec)
+    ref = oracle.apply_A(dims, mass, fat, lng, src)
+    nrm = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
+    say(f"A {dims} prec={prec}: normwise {nrm:.3e}")
+    assert nrm <= tol
