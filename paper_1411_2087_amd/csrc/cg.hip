@@ -103,6 +103,7 @@ __device__ __forceinline__ void finalize(CGState *st, int mode, double v)
         }
         break;
     case FIN_INIT_PLAIN:
+        st->beta = 0.0;  // the first direction is p = r
         st->rr = v;
         st->rr_true = v;
         st->flags.done = (v <= st->stop2) ? CG_CONVERGED : 0;
@@ -131,6 +132,7 @@ __device__ __forceinline__ void finalize(CGState *st, int mode, double v)
         break;
     }
     case FIN_INIT_MIXED:
+        st->beta = 0.0;
         st->rr = v;
         st->maxrr = v;
         st->rr_true = v;
@@ -143,6 +145,12 @@ __device__ __forceinline__ void finalize(CGState *st, int mode, double v)
         break;
     }
 }
+
+}  // namespace hisq
+
+#include "cg_split.hpp"
+
+namespace hisq {
 
 // ------------------------------------------------------------------ BLAS kernels
 // Streaming vector kernels: each thread owns BL_U entries spaced BL_NT apart
@@ -504,20 +512,38 @@ struct NoCheck {
     void operator()(int) const {}
 };
 
+// end_fn(q): enqueued after every group of K iterations, before the state check.
+struct NoEnd {
+    hipError_t operator()(hipStream_t) const { return hipSuccess; }
+};
+
 // on_check(n): called after every state read-back with the number of
 // iterations that ran (were not gated off) since the previous one.
-template <class IterFn, class PauseFn = NoPause, class CheckFn = NoCheck>
-static int run_iterations(IterFn iter_fn, hipStream_t s, CGState *dstate, CGState *hstate, int K, int max_iter,
-                          bool use_graph, int already, PauseFn pause_fn = PauseFn(), CheckFn on_check = CheckFn())
-{
+//
+// adapt (automatic check_every): a pause leaves the rest of its group idle and
+// a check costs a round trip to the host, so after the 1st, 4th and 16th pause
+// the group becomes a whole fraction, at most K, of the iterations from one
+// pause to the next (at 8^4 with 16-bit links, m = 0.08, updates come every
+// ~7 iterations: groups of 8 take 16 us per iteration, groups of 50 take 47).
+struct IterGraph {
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
-    if (use_graph) {
+    void reset()
+    {
+        if (exec) hipGraphExecDestroy(exec);
+        if (graph) hipGraphDestroy(graph);
+        exec = nullptr;
+        graph = nullptr;
+    }
+    ~IterGraph() { reset(); }
+    template <class IterFn, class EndFn> int capture(IterFn &iter_fn, EndFn &end_fn, int K)
+    {
+        reset();
         hipStream_t cs = capture_stream();
         if (!cs) return fail(HISQ_EHIP, "cannot create capture stream");
         HISQ_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < K; ++k) {
-            hipError_t e = iter_fn(cs);
+        for (int k = 0; k <= K; ++k) {
+            hipError_t e = k < K ? iter_fn(cs) : end_fn(cs);
             if (e != hipSuccess) {
                 hipGraph_t junk;
                 hipStreamEndCapture(cs, &junk);
@@ -527,36 +553,59 @@ static int run_iterations(IterFn iter_fn, hipStream_t s, CGState *dstate, CGStat
         }
         HISQ_HIP(hipStreamEndCapture(cs, &graph));
         HISQ_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+        return HISQ_OK;
+    }
+};
+
+template <class IterFn, class PauseFn = NoPause, class CheckFn = NoCheck, class EndFn = NoEnd>
+static int run_iterations(IterFn iter_fn, hipStream_t s, CGState *dstate, CGState *hstate, int K, int max_iter,
+                          bool use_graph, int already, PauseFn pause_fn = PauseFn(), CheckFn on_check = CheckFn(),
+                          EndFn end_fn = EndFn(), bool adapt = false)
+{
+    IterGraph graph;
+    const int K0 = K;
+    int pauses = 0;
+    if (use_graph) {
+        const int rc = graph.capture(iter_fn, end_fn, K);
+        if (rc) return rc;
     }
     int queued = already;
-    int rc = HISQ_OK;
     while (queued < max_iter) {
         const int k = (max_iter - queued) < K ? (max_iter - queued) : K;
         if (use_graph && k == K) {
-            hipError_t e = hipGraphLaunch(exec, s);
-            if (e != hipSuccess) { rc = hip_fail(e, "hipGraphLaunch"); break; }
+            hipError_t e = hipGraphLaunch(graph.exec, s);
+            if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
         } else {
-            for (int i = 0; i < k; ++i) {
-                hipError_t e = iter_fn(s);
-                if (e != hipSuccess) { rc = hip_fail(e, "CG iteration launch"); break; }
+            for (int i = 0; i <= k; ++i) {
+                hipError_t e = i < k ? iter_fn(s) : end_fn(s);
+                if (e != hipSuccess) return hip_fail(e, "CG iteration launch");
             }
-            if (rc) break;
         }
         queued += k;
         const int before = hstate->iter;
         hipError_t e = hipMemcpyAsync(hstate, dstate, sizeof(CGState), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) { rc = hip_fail(e, "CG state read-back"); break; }
+        if (e != hipSuccess) return hip_fail(e, "CG state read-back");
         on_check(hstate->iter - before);
         if (hstate->flags.done) break;
         if (hstate->flags.reliable) {
             e = pause_fn(s);
-            if (e != hipSuccess) { rc = hip_fail(e, "reliable update launch"); break; }
+            if (e != hipSuccess) return hip_fail(e, "reliable update launch");
+            ++pauses;
+            if (adapt && (pauses == 1 || pauses == 4 || pauses == 16)) {
+                const int gap = std::max(1, (hstate->iter - already) / pauses) + 1, groups = (gap + K0 - 1) / K0;
+                const int want = std::max(4, (gap + groups - 1) / groups);
+                if (want != K) {
+                    K = want;
+                    if (use_graph) {
+                        const int rc = graph.capture(iter_fn, end_fn, K);
+                        if (rc) return rc;
+                    }
+                }
+            }
         }
     }
-    if (exec) hipGraphExecDestroy(exec);
-    if (graph) hipGraphDestroy(graph);
-    return rc;
+    return HISQ_OK;
 }
 
 static int read_state(CGState *h, const CGState *d, hipStream_t s)
@@ -763,9 +812,13 @@ int cg_plain(double mass, double tol, const void *fat, const void *lng, const vo
     if (rc) return rc;
     if (hs->bb == 0.0) return zero_source_exit(x, v64, s, stats, t0);
 
+    // timing mode keeps the three kernels it reports
+    SplitIter sp;
+    if (o.use_graph != 2) sp.set(g, PH::prec, st, (char *)(st + 1), (size_t)((char *)r - (char *)(st + 1)));
     IterTimer tm;
     if (o.use_graph == 2 && !tm.start(o.check_every)) return fail(HISQ_EHIP, "cg_solve: event creation failed");
     auto iter = [&](hipStream_t q) -> hipError_t {
+        if (sp.on) return sp.template iteration<PH>(q, g, fat, lng, r, p, t, x, FIN_UPD_PLAIN);
         L.dp<PH>(q, fat, lng, p, t, tm.at(0), tm.at(1));
         L.ap_update<PH>(q, fat, lng, t, p, x, r, FIN_UPD_PLAIN, tm.at(2), tm.at(3));
         L.pupd<double2>(q, p, r, tm.at(4), tm.at(5));
@@ -773,13 +826,14 @@ int cg_plain(double mass, double tol, const void *fat, const void *lng, const vo
         return hipGetLastError();
     };
     auto on_check = [&](int ran) { if (tm.K) tm.collect(ran); };
+    auto settle = [&](hipStream_t q) { return sp.settle(q, g, FIN_UPD_PLAIN); };
 
     int restarts = 0;
     int status = HISQ_OK;
     while (true) {
         if (!hs->flags.done) {
             rc = run_iterations(iter, s, st, hs, o.check_every, o.max_iter, o.use_graph != 0 && o.use_graph != 2, hs->iter, NoPause(),
-                                on_check);
+                                on_check, settle);
             if (rc) return rc;
         }
         if (hs->flags.done == CG_BREAKDOWN) { status = HISQ_EBREAKDOWN; break; }
@@ -825,7 +879,7 @@ template <class PS> constexpr double default_delta()
 
 template <class PH, class PS>
 int cg_mixed(double mass, double tol, const void *fat, const void *lng, const void *fat_lo, const void *lng_lo,
-             const void *b, void *x, const Geom &g, const hisq_cg_opts &o, void *ws, size_t ws_bytes,
+             const void *b, void *x, const Geom &g, const hisq_cg_opts &o, bool adapt, void *ws, size_t ws_bytes,
              hisq_cg_stats &stats, hipStream_t s)
 {
     Carver c{ (char *)ws, ws_bytes };
@@ -857,8 +911,12 @@ int cg_mixed(double mass, double tol, const void *fat, const void *lng, const vo
     if (hs->bb == 0.0) return zero_source_exit(x, v64, s, stats, t0);
 
     const dim3 gb(L.nbl), bb(BL_NT);
+    SplitIter sp;  // its scratch: t64, which only the reliable update uses
+    sp.set(g, PS::prec, st, t64, v64);
+    auto settle = [&](hipStream_t q) { return sp.settle(q, g, FIN_UPD_MIXED); };
     // one inner iteration; a reliable update request pauses the rest of the graph
     auto iter = [&](hipStream_t q) -> hipError_t {
+        if (sp.on) return sp.template iteration<PS>(q, g, fat_lo, lng_lo, rs, ps, ts, xs, FIN_UPD_MIXED);
         L.dp<PS>(q, fat_lo, lng_lo, ps, ts);
         L.ap_update<PS>(q, fat_lo, lng_lo, ts, ps, xs, rs, FIN_UPD_MIXED);
         L.pupd<float2>(q, ps, rs);
@@ -870,11 +928,11 @@ int cg_mixed(double mass, double tol, const void *fat, const void *lng, const vo
         hipError_t e = launch_dslash<PH>(g, fat, lng, x, t64, 1, q, &st->flags, GATE_RELIABLE);
         if (e != hipSuccess) return e;
         L.template resid<PH>(q, fat, lng, t64, x, b, r64, nullptr, rs, nullptr, FIN_RELIABLE, GATE_RELIABLE);
-        L.pupd<float2>(q, ps, rs);
+        if (!sp.on) L.pupd<float2>(q, ps, rs);  // the split iteration takes r + beta p itself
         return hipGetLastError();
     };
 
-    rc = run_iterations(iter, s, st, hs, o.check_every, o.max_iter, o.use_graph != 0, 0, reliable);
+    rc = run_iterations(iter, s, st, hs, o.check_every, o.max_iter, o.use_graph != 0, 0, reliable, NoCheck(), settle, adapt);
     if (rc) return rc;
     if (hs->flags.done == CG_STALLED) {
         // The low-precision operator cannot drive the true residual down: fold
@@ -1025,6 +1083,7 @@ extern "C" int cg_solve(double mass, double tol, const void *fat, const void *ln
     if (!(o.delta < 1.0)) return st.status = fail(HISQ_EINVAL, "cg_solve: opts->delta must be below 1");
     if (!workspace || ws_bytes < cg_workspace_bytes(g, o.mode))
         return st.status = fail(HISQ_EWORKSPACE, "cg_solve: workspace NULL or smaller than hisq_workspace_bytes()");
+    const bool adapt = !opts || opts->check_every <= 0;  // the host check interval is the solver's own
     hipStream_t s = (hipStream_t)stream;
     {
         hipError_t e = hipStreamSynchronize(s);
@@ -1034,19 +1093,19 @@ extern "C" int cg_solve(double mass, double tol, const void *fat, const void *ln
     case HISQ_CG_PLAIN_F64: rc = cg_plain<PF64>(mass, tol, fat, lng, b, x, g, o, workspace, ws_bytes, st, s); break;
     case HISQ_CG_PLAIN_F64C: rc = cg_plain<PF64C>(mass, tol, fat, lng, b, x, g, o, workspace, ws_bytes, st, s); break;
     case HISQ_CG_MIXED_F32:
-        rc = cg_mixed<PF64, PF32>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, workspace, ws_bytes, st, s);
+        rc = cg_mixed<PF64, PF32>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, adapt, workspace, ws_bytes, st, s);
         break;
     case HISQ_CG_MIXED_F16S:
-        rc = cg_mixed<PF64, PF16S>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, workspace, ws_bytes, st, s);
+        rc = cg_mixed<PF64, PF16S>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, adapt, workspace, ws_bytes, st, s);
         break;
     case HISQ_CG_MIXED_I16S:
-        rc = cg_mixed<PF64, PI16S>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, workspace, ws_bytes, st, s);
+        rc = cg_mixed<PF64, PI16S>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, adapt, workspace, ws_bytes, st, s);
         break;
     case HISQ_CG_MIXED_F32C:
-        rc = cg_mixed<PF64C, PF32C>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, workspace, ws_bytes, st, s);
+        rc = cg_mixed<PF64C, PF32C>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, adapt, workspace, ws_bytes, st, s);
         break;
     default:
-        rc = cg_mixed<PF64C, PI16SC>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, workspace, ws_bytes, st, s);
+        rc = cg_mixed<PF64C, PI16SC>(mass, tol, fat, lng, fat_lo, lng_lo, b, x, g, o, adapt, workspace, ws_bytes, st, s);
     }
     st.status = rc;
     return rc;

@@ -38,7 +38,7 @@ struct CGState {
     int last_upd;    // iteration of the last reliable update
     int first_gap;   // iterations from the start to the first reliable update
     int poor;        // consecutive reliable updates that did not halve |r|
-    int pad_;
+    int pending;     // cg_split.hpp: the last iteration's |r|^2 partials are not in the state yet
 };
 
 

@@ -181,3 +181,23 @@ def test_cg_blocked_tile_order(hq, mode):
     say(f"cg blocked order 16^4 mode={mode}: iters {s1['iters']} (plain order {s0['iters']}), oracle_resid={tr:.3e}")
     assert s1["rc"] == 0 and tr <= CG_TOL
     assert abs(s1["iters"] - s0["iters"]) <= 3
+
+
+# two kernels per iteration up to 768 tiles, three up to 1280 (FP64: while the partials fit beside the state), five
+# beyond; 6^4 and 6x4x4x10 have ragged tiles
+@pytest.mark.parametrize("mode", [0, 1, 4, 6])
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 4, 10), (6, 6, 6, 6), (16, 16, 16, 24), (14, 14, 18, 28),
+                                  (20, 16, 16, 32), (18, 18, 22, 24)], ids=lambda d: "x".join(map(str, d)))
+def test_cg_kernel_forms(hq, dims, mode):
+    """Every form of the iteration solves to tol, and its result does not depend on how the iterations are grouped:
+    as graphs of the solver's own size, as single launches, or in groups of 7."""
+    mass = 0.2
+    fat, lng = fields(dims, synth.gauge_seed(14))
+    b = synth.source(dims, synth.source_seed(14))
+    x, st = _solve(hq, dims, fat, lng, b, mass, mode)
+    tr = oracle.true_residual(dims, mass, fat, lng, b, x)
+    say(f"cg forms {dims} mode={mode}: iters={st['iters']} updates={st['reliable_updates']} oracle_resid={tr:.3e}")
+    assert st["rc"] == 0 and tr <= CG_TOL and st["fallback_used"] == 0
+    for kw in (dict(use_graph=0), dict(check_every=7)):
+        y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, **kw)
+        assert s2["iters"] == st["iters"] and np.array_equal(x, y)
