@@ -7,10 +7,13 @@
 // matrix; the 3x3 complex products run in FP64 registers.  All indexing is
 // periodic: the boundary sign enters only through hisq_fold_links.
 #include <cmath>
+#include <type_traits>
 
 #include "hisq_common.hpp"
 
 namespace hisq {
+
+constexpr int LNT = 256;
 
 struct M3 {
     double2 e[9];
@@ -223,6 +226,338 @@ __global__ void __launch_bounds__(NT) k_staple(Lex g, const double2 *__restrict_
     }
 }
 
+// ------------------------------------------------------------------ path sums in three passes
+// With T_k V = the 3-staple of the field V in the direction k (both signs), the
+// path sum of a link direction mu is linear in its nested staples:
+//   V_k = c5 U_mu + c7 T_k U_mu                               (3 staples)
+//   X_o = c3 U_mu + sum_{i != o} T_i V_k                      (6; k the axis other than mu, o, i)
+//   F   = c1 U_mu + sum_o T_o X_o + cL sum_o (T_o^+ T_o^+ + T_o^- T_o^-) U_mu
+// that is 12 staples and the Lepage paths instead of one staple per member of
+// the path families (21), and three launches per mu instead of 27.
+//
+// Fields are in 64-site tiles [tile][element][site], so that a wavefront's
+// loads are contiguous, with the sites numbered in blocks of 4 (or 2) along
+// each axis: 256 consecutive sites are a 4^4 block where the extents allow it.
+// The thin links are brought into that form once; F leaves it through LDS.
+//
+// What bounds the passes is the fabric: with one site per thread, nothing
+// staged and lexicographic order, an XCD's wavefronts touch 10 MB between two
+// uses of a line, so three reads in four miss its 4 MB L2 and the passes ran
+// at 7 TB/s on 4-6 times the fields (32^4: V 0.37, X 0.85, F 0.65 ms per mu).
+// Workgroups that hold their block's thin links (or V) in LDS read only the
+// faces again: X 6.0 -> 1.7 GB and 0.57 ms, F 4.3 -> 3.6 GB and 0.55 ms, V
+// unchanged.  The path sum at 32^4: 21.0 ms staple by staple, 5.9 ms.
+struct PathGeo {
+    Lex g;
+    int lb[4], is[4], ts[4];  // block extents 2^lb; strides inside a block and between blocks
+    int lt;                   // sites of a block, 2^lt
+    const double2 *U;         // four fields of `stride` double2
+    double2 *V, *X;           // three each
+    size_t stride;
+    int ntiles;
+};
+
+__device__ __forceinline__ M3 ld_tile(const double2 *__restrict__ f, int n)
+{
+    const double2 *p = f + (size_t)(n >> 6) * (9 * TILE) + (n & 63);
+    M3 m;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m.e[e] = p[e * TILE];
+    return m;
+}
+__device__ __forceinline__ void st_tile(double2 *__restrict__ f, int n, const M3 &m)
+{
+    double2 *p = f + (size_t)(n >> 6) * (9 * TILE) + (n & 63);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) p[e * TILE] = m.e[e];
+}
+
+// The site: its number n in the blocked order and lex in the canonical one,
+// and its moves along each axis in n: up[d], dn[d] to the next and the
+// previous site, up2, dn2 two away.  Moves along different axes add.
+struct PathSite {
+    int n, up[4], dn[4], up2[4], dn2[4];
+    long long lex;
+    bool live;
+};
+__device__ __forceinline__ int pick(const int v[4], int i) { return i == 0 ? v[0] : i == 1 ? v[1] : i == 2 ? v[2] : v[3]; }
+__device__ __forceinline__ PathSite path_site(const PathGeo &p, long long n)
+{
+    PathSite s;
+    s.live = n < p.g.V;
+    s.n = s.live ? (int)n : (int)p.g.V - 1;
+    s.lex = 0;
+    int in = s.n & ((1 << p.lt) - 1), b = s.n >> p.lt;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int L = p.g.L[d], lb = p.lb[d], nb_d = L >> lb, bc = b % nb_d;
+        const int c = (bc << lb) + (in & ((1 << lb) - 1));
+        b /= nb_d;
+        in >>= lb;
+        s.lex += c * p.g.s[d];
+        auto at = [&](int v) {
+            v += v < 0 ? L : 0;
+            v -= v >= L ? L : 0;
+            return (v >> lb) * p.ts[d] + (v & ((1 << lb) - 1)) * p.is[d];
+        };
+        const int here = at(c);
+        s.up[d] = at(c + 1) - here;
+        s.dn[d] = at(c - 1) - here;
+        s.up2[d] = at(c + 2) - here;
+        s.dn2[d] = at(c - 2) - here;
+    }
+    return s;
+}
+
+// the directions other than MU, in order
+template <int MU> __device__ constexpr int other(int j) { return j < MU ? j : j + 1; }
+
+// S += av b^dag (up) or av b (down)
+template <bool DOWN> __device__ __forceinline__ void add_right(M3 &S, const M3 &av, const M3 &b)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            double re = S.e[3 * i + j].x, im = S.e[3 * i + j].y;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double2 x = av.e[3 * i + k], y = DOWN ? b.e[3 * k + j] : b.e[3 * j + k];
+                const double yi = DOWN ? y.y : -y.y;
+                re = fma(x.x, y.x, re);
+                re = fma(-x.y, yi, re);
+                im = fma(x.x, yi, im);
+                im = fma(x.y, y.x, im);
+            }
+            S.e[3 * i + j] = make_double2(re, im);
+        }
+}
+
+// An index offset of 0 that the compiler takes to depend on m: what is loaded
+// through it is not loaded before m is there.
+__device__ __forceinline__ void after(int &zero, const M3 &m)
+{
+    asm volatile("" : "+v"(zero) : "v"(m.e[0].x), "v"(m.e[4].y), "v"(m.e[8].x), "v"(m.e[8].y));
+}
+// S += a v b^dag (up) or a^dag v b (down), the two halves of a staple, on
+// operands loaded when their turn comes (each takes `zero`): b when a and v
+// are consumed, and nothing of the next staple before that.  Three matrices
+// and the sum are what a thread's registers hold at 3 wavefronts per SIMD.
+struct NoInit {};
+// init: where S comes from, if it is not there yet
+template <bool DOWN, class FA, class FV, class FB, class FS = NoInit>
+__device__ __forceinline__ void load_staple(M3 &S, int &zero, FA a, FV v, FB b, FS init = FS())
+{
+    M3 av;
+    {
+        const M3 x = a(), y = v();
+        av = mm<DOWN, false>(x, y);
+    }
+    after(zero, av);
+    if constexpr (!std::is_same<FS, NoInit>::value) S = init();
+    add_right<DOWN>(S, av, b());
+    after(zero, S);
+}
+
+__device__ __forceinline__ M3 scaled(double c, const M3 &m)
+{
+    M3 r;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) r.e[i] = make_double2(c * m.e[i].x, c * m.e[i].y);
+    return r;
+}
+
+// canonical thin links to the blocked tiles, one direction per blockIdx.y
+__global__ void __launch_bounds__(LNT) k_path_tiles(PathGeo p, const double2 *__restrict__ thin, double2 *__restrict__ U)
+{
+    __shared__ Stage<LNT> st;
+    const PathSite s = path_site(p, (long long)blockIdx.x * LNT + threadIdx.x);
+    const M3 m = gather<LNT>(st, thin + 9 * (size_t)blockIdx.y * p.g.V, s.live ? s.lex : -1);
+    if (s.live) st_tile(U + blockIdx.y * p.stride, s.n, m);
+}
+
+// ---- the three passes: 256 consecutive sites per workgroup, three threads per
+// site, one for each axis other than mu (group j, four wavefronts).  The
+// sites' own matrices of the thin fields (and of V) are in LDS, so that what
+// a hop finds inside the workgroup's block is read there; only the block's
+// faces come from memory again.
+constexpr int PNT = 3 * LNT;
+constexpr int PTILE = 9 * LNT;  // double2 of one field's block: four tiles
+
+struct PathLds {
+    double2 t[4][PTILE];
+};
+static_assert(sizeof(PathLds) <= 160 * 1024, "LDS of a CU");
+
+// Site n of field f, whose block of sites n0 .. n0 + 255 has its image in t:
+// a lane's address is in one or the other, one load instruction serves both
+// (branches per matrix instead of flat addresses spill 60-360 registers).
+__device__ __forceinline__ M3 ld_block(const double2 *t, const double2 *f, int n, int n0)
+{
+    const int q = n - n0;
+    const double2 *in = t + (q >> 6) * (9 * TILE) + (q & 63), *out = f + (size_t)(n >> 6) * (9 * TILE) + (n & 63);
+    const double2 *p = (unsigned)q < (unsigned)LNT ? in : out;
+    M3 m;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m.e[e] = p[e * TILE];
+    return m;
+}
+// the block's image (zero past the lattice's last tile)
+__device__ __forceinline__ void copy_block(double2 *t, const double2 *__restrict__ f, int n0, int ntiles)
+{
+    const double2 *b = f + (size_t)(n0 >> 6) * (9 * TILE);
+    const int have = min(PTILE, (ntiles - (n0 >> 6)) * 9 * TILE);
+    for (int q = threadIdx.x; q < PTILE; q += PNT) t[q] = q < have ? b[q] : make_double2(0.0, 0.0);
+}
+
+// V_k = c5 U_mu + c7 A_k for the three axes k.  SEVEN: c7 is not zero.
+template <int MU, bool SEVEN> __global__ void __launch_bounds__(PNT) k_path_v(PathGeo p, double c5, double c7)
+{
+    __shared__ PathLds l;
+    const int blk = xcd_block(blockIdx.x, gridDim.x), j = __builtin_amdgcn_readfirstlane(threadIdx.x / LNT);
+    const int i = threadIdx.x % LNT, n0 = blk * LNT, k = other<MU>(j);
+    if ((long long)n0 >= p.g.V) return;
+    const PathSite s = path_site(p, n0 + i);
+    const double2 *Um = p.U + MU * p.stride, *Uk = p.U + k * p.stride;
+    M3 S;
+    int zero = 0;
+    if constexpr (SEVEN) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f) copy_block(l.t[f], p.U + other<MU>(f) * p.stride, n0, p.ntiles);
+        copy_block(l.t[3], Um, n0, p.ntiles);
+        __syncthreads();
+        const int up = pick(s.up, k), m = s.n + pick(s.dn, k);
+        auto uk = [&](int n) { return [&, n] { return ld_block(l.t[j], Uk, n + zero, n0); }; };
+        auto um = [&](int n) { return [&, n] { return ld_block(l.t[3], Um, n + zero, n0); }; };
+        load_staple<false>(S, zero, uk(s.n), um(s.n + up), uk(s.n + s.up[MU]), [] { return scaled(0.0, M3{}); });
+        load_staple<true>(S, zero, uk(m), um(m), uk(m + s.up[MU]));
+        const M3 u = ld_tile(l.t[3], i + zero);
+#pragma unroll
+        for (int e = 0; e < 9; ++e)
+            S.e[e] = make_double2(fma(c7, S.e[e].x, c5 * u.e[e].x), fma(c7, S.e[e].y, c5 * u.e[e].y));
+    } else {
+        S = scaled(c5, ld_tile(Um, s.n));
+    }
+    if (s.live) st_tile(p.V + j * p.stride, s.n, S);
+}
+
+// X_o for the three axes o: V_k of the block in t[k], U_i of one axis after the other in t[3].
+template <int MU> __global__ void __launch_bounds__(PNT) k_path_x(PathGeo p, double c3)
+{
+    __shared__ PathLds l;
+    const int blk = xcd_block(blockIdx.x, gridDim.x), o = __builtin_amdgcn_readfirstlane(threadIdx.x / LNT);
+    const int i = threadIdx.x % LNT, n0 = blk * LNT;
+    if ((long long)n0 >= p.g.V) return;
+    const PathSite s = path_site(p, n0 + i);
+#pragma unroll
+    for (int f = 0; f < 3; ++f) copy_block(l.t[f], p.V + f * p.stride, n0, p.ntiles);
+    M3 X = scaled(c3, ld_tile(p.U + MU * p.stride, s.n));
+    int zero = 0;
+#pragma unroll 1
+    for (int ji = 0; ji < 3; ++ji) {
+        const int d = other<MU>(ji), k = 3 - ji - o;
+        const double2 *Ui = p.U + d * p.stride;
+        if (ji) __syncthreads();  // the previous axis is done with t[3]
+        copy_block(l.t[3], Ui, n0, p.ntiles);
+        __syncthreads();
+        if (ji == o) continue;
+        const double2 *Vk = p.V + k * p.stride;
+        const int up = pick(s.up, d), m = s.n + pick(s.dn, d);
+        auto ui = [&](int n) { return [&, n] { return ld_block(l.t[3], Ui, n + zero, n0); }; };
+        auto vk = [&](int n) { return [&, n] { return ld_block(l.t[k], Vk, n + zero, n0); }; };
+        load_staple<false>(X, zero, ui(s.n), vk(s.n + up), ui(s.n + s.up[MU]));
+        load_staple<true>(X, zero, ui(m), vk(m), ui(m + s.up[MU]));
+    }
+    if (s.live) st_tile(p.X + o * p.stride, s.n, X);
+}
+
+// F.  HASX: X holds the inner sums; else they are c3 U_mu alone (c3 may be 0).  LEP: the Lepage paths.
+template <int MU, bool HASX, bool LEP>
+__global__ void __launch_bounds__(PNT) k_path_f(PathGeo p, double2 *__restrict__ F, double c1, double c3, double cl)
+{
+    __shared__ PathLds l;
+    __shared__ long long lex[LNT];
+    const int blk = xcd_block(blockIdx.x, gridDim.x), j = __builtin_amdgcn_readfirstlane(threadIdx.x / LNT);
+    const int i = threadIdx.x % LNT, n0 = blk * LNT, o = other<MU>(j);
+    if ((long long)n0 >= p.g.V) return;
+    const PathSite s = path_site(p, n0 + i);
+    const double2 *Um = p.U + MU * p.stride, *Uo = p.U + o * p.stride, *Xo = p.X + j * p.stride;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) copy_block(l.t[b], p.U + other<MU>(b) * p.stride, n0, p.ntiles);
+    copy_block(l.t[3], Um, n0, p.ntiles);
+    if (j == 0) lex[i] = s.live ? s.lex : -1;
+    __syncthreads();
+    M3 f = scaled(j == 0 ? c1 : 0.0, ld_tile(l.t[3], i));
+    int zero = 0;
+    const int up = pick(s.up, o), dn = pick(s.dn, o);
+    auto half = [&](auto dir) {
+        constexpr bool DN = decltype(dir)::value;
+        const int at = DN ? s.n + dn : s.n, v = DN ? at : s.n + up;
+        auto uo = [&](int n) { return [&, n] { return ld_block(l.t[j], Uo, n + zero, n0); }; };
+        auto um = [&](int n) { return [&, n] { return ld_block(l.t[3], Um, n + zero, n0); }; };
+        auto inner = [&] { return HASX ? ld_tile(Xo, v + zero) : scaled(c3, um(v)()); };
+        M3 w;
+        if constexpr (LEP) {
+            // the half staple of U_mu at v on the same side
+            const int q = DN ? s.n + pick(s.dn2, o) : v, u = DN ? q : s.n + pick(s.up2, o);
+            load_staple<DN>(w, zero, [&] { return scaled(cl, uo(q)()); }, um(u), uo(q + s.up[MU]), inner);
+        } else {
+            w = inner();
+        }
+        load_staple<DN>(f, zero, uo(at), [&] { return w; }, uo(at + s.up[MU]));
+    };
+    half(std::false_type{});
+    half(std::true_type{});
+    // the three groups' sums in order, then out in the canonical form: [site][element] in t[0]
+    __syncthreads();
+    st_tile(l.t[1 + j], i, f);
+    __syncthreads();
+    for (int q = threadIdx.x; q < PTILE; q += PNT) {
+        const double2 a = l.t[1][q], b = l.t[2][q], c = l.t[3][q];
+        const int tile = q / (9 * TILE), r = q % (9 * TILE);
+        l.t[0][9 * (tile * TILE + r % TILE) + r / TILE] = make_double2((a.x + b.x) + c.x, (a.y + b.y) + c.y);
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < PTILE; q += PNT) {
+        const long long n = lex[q / 9];
+        if (n >= 0) ntstore(l.t[0][q], F + 9 * n + q % 9);
+    }
+}
+
+static PathGeo path_geo(const Lex &l)
+{
+    PathGeo p;
+    p.g = l;
+    p.lt = 0;
+    for (int d = 0; d < 4; ++d) {
+        p.lb[d] = l.L[d] % 4 == 0 ? 2 : 1;
+        p.is[d] = 1 << p.lt;
+        p.lt += p.lb[d];
+    }
+    int t = 1 << p.lt;
+    for (int d = 0; d < 4; ++d) {
+        p.ts[d] = t;
+        t *= l.L[d] >> p.lb[d];
+    }
+    return p;
+}
+
+template <int MU>
+static void launch_paths(const PathGeo &p, double2 *F, const double c[5], hipStream_t s)
+{
+    const double c1 = c[0], c3 = c[1], c5 = c[2], c7 = c[3], cl = c[4];
+    const dim3 grid(xcd_grid((int)((p.g.V + LNT - 1) / LNT))), blk(PNT);
+    const bool x = c5 != 0 || c7 != 0;
+    if (x) {
+        auto kv = c7 != 0 ? k_path_v<MU, true> : k_path_v<MU, false>;
+        hipLaunchKernelGGL(kv, grid, blk, 0, s, p, c5, c7);
+        hipLaunchKernelGGL(k_path_x<MU>, grid, blk, 0, s, p, c3);
+    }
+    auto kf = x ? (cl != 0 ? k_path_f<MU, true, true> : k_path_f<MU, true, false>)
+                : (cl != 0 ? k_path_f<MU, false, true> : k_path_f<MU, false, false>);
+    hipLaunchKernelGGL(kf, grid, blk, 0, s, p, F, c1, c3, cl);
+}
+
 // out = c U (the one-link term alone, when no staple is summed)
 template <int NT>
 __global__ void __launch_bounds__(NT) k_scale_links(long long n9, const double2 *__restrict__ in,
@@ -273,8 +608,6 @@ static bool overlaps(const void *a, size_t na, const void *b, size_t nb)
     return x < y + nb && y < x + na;
 }
 
-constexpr int LNT = 256;
-
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 static int check_launch(const char *what)
@@ -283,11 +616,17 @@ static int check_launch(const char *what)
     return e == hipSuccess ? HISQ_OK : hip_fail(e, what);
 }
 
+// One tiled field, and the workspace of the three-pass schedule: the four
+// thin fields, A and X (three each).  A caller with room for three fields only
+// gets the staple-by-staple schedule.
+static size_t tiled_field_bytes(const Lex &l) { return (size_t)((l.V + TILE - 1) / TILE) * TILE * 144; }
+static size_t fat_paths_min_bytes(const Lex &l) { return 3 * align_up((size_t)l.V * 144, 256); }
+
 size_t fat_paths_ws_bytes(const int dims[4])
 {
     Lex l;
     if (make_lex(dims, l)) return 0;
-    return 3 * align_up((size_t)l.V * 144, 256);
+    return 10 * tiled_field_bytes(l);
 }
 
 }  // namespace hisq
@@ -323,7 +662,8 @@ extern "C" int hisq_fat_paths(const void *thin, const double coeff[5], void *out
         if (!std::isfinite(coeff[i])) return fail(HISQ_EINVAL, "hisq_fat_paths: coefficient not finite");
     const size_t bytes = (size_t)l.V * 4 * 144;
     if (overlaps(thin, bytes, out, bytes)) return fail(HISQ_EALIAS, "hisq_fat_paths: out overlaps thin");
-    const size_t need = fat_paths_ws_bytes(dims);
+    const bool passes = ws_bytes >= fat_paths_ws_bytes(dims) && l.V < (1LL << 31);  // sites are ints there
+    const size_t need = passes ? fat_paths_ws_bytes(dims) : fat_paths_min_bytes(l);
     if (!workspace || ws_bytes < need)
         return fail(HISQ_EWORKSPACE, "hisq_fat_paths: workspace NULL or smaller than hisq_workspace_bytes()");
     if (overlaps(workspace, need, thin, bytes) || overlaps(workspace, need, out, bytes))
@@ -337,6 +677,21 @@ extern "C" int hisq_fat_paths(const void *thin, const double coeff[5], void *out
     const dim3 grid((unsigned)((l.V + LNT - 1) / LNT)), blk(LNT);
     const double2 *U = (const double2 *)thin;
     const bool need3 = c3 != 0 || c5 != 0 || c7 != 0;
+    if (passes && (need3 || cl != 0)) {
+        PathGeo p = path_geo(l);
+        p.stride = tiled_field_bytes(l) / 16;
+        p.ntiles = (int)(p.stride / (9 * TILE));
+        p.U = (const double2 *)workspace;
+        p.V = (double2 *)workspace + 4 * p.stride;
+        p.X = (double2 *)workspace + 7 * p.stride;
+        hipLaunchKernelGGL(k_path_tiles, dim3(grid.x, 4), blk, 0, s, p, U, (double2 *)workspace);
+        double2 *F = (double2 *)out;
+        launch_paths<0>(p, F, coeff, s);
+        launch_paths<1>(p, F + 9 * (size_t)l.V, coeff, s);
+        launch_paths<2>(p, F + 18 * (size_t)l.V, coeff, s);
+        launch_paths<3>(p, F + 27 * (size_t)l.V, coeff, s);
+        return check_launch("hisq_fat_paths");
+    }
     for (int mu = 0; mu < 4; ++mu) {
         const double2 *Umu = U + 9 * (size_t)mu * l.V;
         double2 *F = (double2 *)out + 9 * (size_t)mu * l.V;

@@ -131,3 +131,24 @@ def test_link_errors(hq):
         hq.hisq_fat_paths(U, (float("nan"), 0, 0, 0, 0), torch.empty_like(U), dims,
                           hq.fields.workspace("fat_paths", dims))
     assert e.value.code == hq.HISQ_EINVAL
+
+
+@pytest.mark.parametrize("dims", [(6, 6, 10, 6), (4, 6, 8, 10), (12, 8, 4, 6)], ids=lambda d: "x".join(map(str, d)))
+@pytest.mark.parametrize("coeff", [(0.4, 0, -0.2, 0, 0), (0.1, 0, 0, 0.3, 0), (0, 0.2, 0.1, 0, 0.3), (0.3, 0, 0, 0, 0.2),
+                                   (0, 0, 0, 0, 0)], ids=lambda c: "_".join(map(str, c)))
+def test_fat_paths_coefficients_and_workspaces(hq, dims, coeff):
+    """Every combination of path families, on lattices whose blocks are 2 or 4 wide, with the full workspace and
+    with one of three fields."""
+    import torch
+    U = synth.thin_links(dims, synth.gauge_seed(8))
+    ref = K.fat_paths(dims, U, coeff)
+    field = (U.shape[1] * 144 + 255) // 256 * 256
+    for ws in (hq.fields.workspace("fat_paths", dims), torch.empty(3 * field, dtype=torch.uint8, device="cuda")):
+        out = torch.full((4, U.shape[1], 3, 3), float("nan"), dtype=torch.complex128, device="cuda")
+        hq.hisq_fat_paths(dev(U), coeff, out, dims, ws)
+        err = np.max(np.abs(out.cpu().numpy() - ref)) / max(bound(coeff), 1e-300)
+        say(f"fat paths {dims} {coeff} workspace {ws.numel()}: max abs error / bound {err:.2e}")
+        assert err <= TOL
+    with pytest.raises(hq.HisqError) as e:
+        hq.hisq_fat_paths(dev(U), coeff, out, dims, torch.empty(3 * field - 16, dtype=torch.uint8, device="cuda"))
+    assert e.value.code == hq.HISQ_EWORKSPACE
