@@ -7,7 +7,9 @@
 // links at the output site doubles the storage but makes every link read of
 // the Dslash contiguous and single-use, the locality argument of Sec. 4
 // ("both forward and backward links are stored at each site").
-#include "hisq_common.hpp"
+#include <type_traits>
+
+#include "canon.hpp"
 
 namespace hisq {
 
@@ -19,7 +21,7 @@ __device__ __forceinline__ void store_block<HISQ_F64>(char *blk, int lane, const
 {
     double2 *p = reinterpret_cast<double2 *>(blk) + lane;
 #pragma unroll
-    for (int e = 0; e < 9; ++e) p[e * TILE] = make_double2(m[2 * e], m[2 * e + 1]);
+    for (int e = 0; e < 9; ++e) ntstore(make_double2(m[2 * e], m[2 * e + 1]), p + e * TILE);
 }
 
 template <>
@@ -77,89 +79,12 @@ __device__ __forceinline__ void store_block<HISQ_I16S>(char *blk, int lane, cons
     *p2 = make_uint2(w[8], __float_as_uint(scale));
 }
 
-template <int PREC>
-__global__ __launch_bounds__(256) void k_pack(const double2 *__restrict__ canon, char *__restrict__ out, Geom g,
-                                              int hop, size_t block_bytes)
-{
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = 2LL * g.ntiles * 8 * TILE;
-    if (i >= total) return;
-    const int lane = (int)(i % TILE);
-    const long long rest = i / TILE;
-    const int d = (int)(rest % 8);
-    const long long pt = rest / 8;  // parity * ntiles + tile
-    const int tile = (int)(pt % g.ntiles);
-    const int parity = (int)(pt / g.ntiles);
-    const int h = tile * TILE + lane;
-    double m[18];
-#pragma unroll
-    for (int e = 0; e < 18; ++e) m[e] = 0.0;
-    if (h < g.Vh) {
-        int c[4];
-        site_coords(g, h, parity, c[0], c[1], c[2], c[3]);
-        const int mu = d & 3;
-        const bool bwd = d >= 4;
-        if (bwd) c[mu] = wrap(c[mu] - hop, g.L[mu]);
-        const long long V = 2LL * g.Vh;
-        const long long lex = c[0] + (long long)g.L[0] * (c[1] + (long long)g.L[1] * (c[2] + (long long)g.L[2] * c[3]));
-        const double2 *u = canon + (mu * V + lex) * 9;
-        if (!bwd) {
-#pragma unroll
-            for (int e = 0; e < 9; ++e) { double2 v = u[e]; m[2 * e] = v.x; m[2 * e + 1] = v.y; }
-        } else {
-            // -U^dag: entry (a, b) = -conj(U_ba)
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    double2 v = u[3 * b + a];
-                    m[2 * (3 * a + b)] = -v.x;
-                    m[2 * (3 * a + b) + 1] = v.y;
-                }
-        }
-    }
-    char *blk = out + ((size_t)pt * 8 + d) * block_bytes;
-    store_block<PREC>(blk, lane, m);
-}
-
-// Two-row long links: rows 0 and 1 of every matrix, plus the sign word of
-// each (tile, direction) built with a wavefront ballot.  `status` is set when
-// a matrix is not +-SU(3) to 1e-6 (padding lanes are exempt).
 template <int PREC, class R>
-__global__ __launch_bounds__(256) void k_pack_rows(const double2 *__restrict__ canon, char *__restrict__ out, Geom g,
-                                                   int hop, int *status)
+__device__ __forceinline__ void store_rows(char *tile_base, int d, int lane, const double m[18], bool valid, int *status)
 {
-    constexpr size_t BB = R::block_bytes, TB = R::tile_bytes;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = 2LL * g.ntiles * 8 * TILE;  // a multiple of 64: whole wavefronts only
-    if (i >= total) return;
-    const int lane = (int)(i % TILE);
-    const long long rest = i / TILE;
-    const int d = (int)(rest % 8);
-    const long long pt = rest / 8;
-    const int tile = (int)(pt % g.ntiles), parity = (int)(pt / g.ntiles);
-    const int h = tile * TILE + lane;
-    double m[18];
-#pragma unroll
-    for (int e = 0; e < 18; ++e) m[e] = 0.0;
+    constexpr size_t BB = R::block_bytes;
     bool neg = false;
-    if (h < g.Vh) {
-        int c[4];
-        site_coords(g, h, parity, c[0], c[1], c[2], c[3]);
-        const int mu = d & 3;
-        const bool bwd = d >= 4;
-        if (bwd) c[mu] = wrap(c[mu] - hop, g.L[mu]);
-        const long long V = 2LL * g.Vh;
-        const long long lex = c[0] + (long long)g.L[0] * (c[1] + (long long)g.L[1] * (c[2] + (long long)g.L[2] * c[3]));
-        const double2 *u = canon + (mu * V + lex) * 9;
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const double2 v = bwd ? u[3 * b + a] : u[3 * a + b];
-                m[2 * (3 * a + b)] = bwd ? -v.x : v.x;
-                m[2 * (3 * a + b) + 1] = v.y;
-            }
+    if (valid) {
         // det by cofactors of row 0; c = sign(Re det)
         const double c0r = m[8] * m[16] - m[9] * m[17] - (m[10] * m[14] - m[11] * m[15]);
         const double c0i = m[8] * m[17] + m[9] * m[16] - (m[10] * m[15] + m[11] * m[14]);
@@ -182,12 +107,11 @@ __global__ __launch_bounds__(256) void k_pack_rows(const double2 *__restrict__ c
         if (!(dev <= 1e-6)) atomicOr(status, 1);
     }
     const unsigned long long word = __ballot(neg);
-    char *tile_base = out + (size_t)pt * TB;
     if (lane == 0) *reinterpret_cast<unsigned long long *>(tile_base + 8 * BB + 8 * (size_t)d) = word;
     if constexpr (PREC == HISQ_F64C) {
         double2 *q = reinterpret_cast<double2 *>(tile_base + (size_t)d * BB) + lane;
 #pragma unroll
-        for (int e = 0; e < 6; ++e) q[e * TILE] = make_double2(m[2 * e], m[2 * e + 1]);
+        for (int e = 0; e < 6; ++e) ntstore(make_double2(m[2 * e], m[2 * e + 1]), q + e * TILE);
     } else if constexpr (PREC == HISQ_I16SC) {
         // rows 0 and 1 in 16-bit fixed point against their largest |re|, |im|
         double mx = 0.0;
@@ -212,6 +136,73 @@ __global__ __launch_bounds__(256) void k_pack_rows(const double2 *__restrict__ c
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             q[k * TILE] = make_float4((float)m[4 * k], (float)m[4 * k + 1], (float)m[4 * k + 2], (float)m[4 * k + 3]);
+    }
+}
+
+// Two consecutive tiles of both parities per workgroup (256 consecutive
+// canonical sites), direction by direction: the workgroup brings the 256
+// source matrices through LDS, so that its loads are contiguous, and each
+// wavefront takes the 64 of its (tile, parity).  A lane that reads its own
+// matrix touches 64 cache lines with every 16-byte load, half of each for the
+// other parity (32^4, us per field: F64 544 -> 436, F64C long 516 -> 311, I16S
+// 342 -> 238, I16SC long 860 -> 229).  Bound by the fabric at 5.5-6.7 TB/s: the
+// canonical field comes twice (forward and, `hop` away, backward), the packed
+// one goes out once, in FP64 with streaming stores (through the caches: 478
+// and 372 us).
+//
+// ROWS = void: full matrices of precision PREC.  Else the two-row form: rows 0
+// and 1 of every matrix, plus the sign word of each (tile, direction) built
+// with a wavefront ballot; `status` is set when a matrix is not +-SU(3) to
+// 1e-6 (padding lanes are exempt).
+constexpr int PACK_NT = 256;
+template <int PREC, class ROWS>
+__global__ __launch_bounds__(PACK_NT) void k_pack(Lex l, Geom g, const double2 *__restrict__ canon,
+                                                  char *__restrict__ out, int hop, size_t block_bytes, int *status)
+{
+    __shared__ Stage<PACK_NT> st;
+    const int blk = xcd_block(blockIdx.x, gridDim.x);
+    const long long n = (long long)blk * PACK_NT + threadIdx.x;
+    if ((long long)blk * PACK_NT >= l.V) return;
+    int cs[4] = { 0, 0, 0, 0 };
+    if (n < l.V) lex_coords(l, n, cs);
+    // this wavefront's tile and parity; its lane's site is canonical site 2 h + bit
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, parity = w & 1, tile = 2 * blk + (w >> 1);
+    const int h = tile * TILE + lane;
+    const bool valid = h < g.Vh;
+    int c[4];
+    site_coords(g, valid ? h : g.Vh - 1, parity, c[0], c[1], c[2], c[3]);
+    const int mine = 2 * TILE * (w >> 1) + 2 * lane + (c[0] & 1);
+    const long long pt = (long long)parity * g.ntiles + tile;
+    // blockIdx.y: this workgroup's share of the 8 directions, each axis's two together
+    const int per = 8 / gridDim.y;
+#pragma unroll 1
+    for (int k = blockIdx.y * per; k < (int)(blockIdx.y + 1) * per; ++k) {
+        const int mu = k >> 1, d = mu + 4 * (k & 1);
+        const bool bwd = d >= 4;
+        long long src = -1;
+        if (n < l.V) src = (long long)mu * l.V + (bwd ? lex_hop(l, n, cs, mu, -hop) : n);
+        stage_in<PACK_NT>(st, canon, src);
+        if (tile >= g.ntiles) continue;  // wave-uniform; the barriers are in stage_in
+        double m[18];
+#pragma unroll
+        for (int e = 0; e < 18; ++e) m[e] = 0.0;
+        if (valid) {
+            const double2 *u = st.m + 9 * mine;
+            // backward: -U^dag, entry (a, b) = -conj(U_ba)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const double2 v = u[bwd ? 3 * b + a : 3 * a + b];
+                    m[2 * (3 * a + b)] = bwd ? -v.x : v.x;
+                    m[2 * (3 * a + b) + 1] = v.y;
+                }
+        }
+        if constexpr (std::is_void<ROWS>::value) {
+            store_block<PREC>(out + ((size_t)pt * 8 + d) * block_bytes, lane, m);
+        } else {
+            store_rows<PREC, ROWS>(out + (size_t)pt * ROWS::tile_bytes, d, lane, m, valid, status);
+        }
     }
 }
 
@@ -269,28 +260,25 @@ extern "C" int hisq_pack_links(const void *fat_canon, const void *long_canon, co
     const size_t bb = dir_block_bytes(prec);
     if (!bb) return fail(HISQ_EINVAL, "hisq_pack_links: unknown precision");
     hipStream_t s = (hipStream_t)stream;
-    const long long total = 2LL * g.ntiles * 8 * TILE;
-    const dim3 grid((unsigned)((total + 255) / 256)), block(256);
+    Lex l;
+    if (make_lex(dims, l)) return HISQ_EDIMS;
+    // where the sites alone do not fill the chip (4 workgroups per CU), the directions are shared out too
+    const int nb = (int)((l.V + PACK_NT - 1) / PACK_NT), split = nb >= 1024 ? 1 : nb >= 256 ? 4 : 8;
+    const dim3 grid(xcd_grid(nb), split), block(PACK_NT);
+    auto full = [&](auto kernel, const void *in, void *out, int hop, size_t bytes) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, l, g, (const double2 *)in, (char *)out, hop, bytes,
+                           (int *)nullptr);
+    };
     if (prec == HISQ_F64C || prec == HISQ_F32C || prec == HISQ_I16SC) {
         const int fp = prec == HISQ_F64C ? HISQ_F64 : (prec == HISQ_F32C ? HISQ_F32 : HISQ_I16S);
-        const size_t fbb = dir_block_bytes(fp);
-        if (fp == HISQ_F64)
-            hipLaunchKernelGGL(k_pack<HISQ_F64>, grid, block, 0, s, (const double2 *)fat_canon, (char *)fat_out, g, 1, fbb);
-        else if (fp == HISQ_F32)
-            hipLaunchKernelGGL(k_pack<HISQ_F32>, grid, block, 0, s, (const double2 *)fat_canon, (char *)fat_out, g, 1, fbb);
-        else
-            hipLaunchKernelGGL(k_pack<HISQ_I16S>, grid, block, 0, s, (const double2 *)fat_canon, (char *)fat_out, g, 1, fbb);
+        full(fp == HISQ_F64 ? k_pack<HISQ_F64, void> : fp == HISQ_F32 ? k_pack<HISQ_F32, void> : k_pack<HISQ_I16S, void>,
+             fat_canon, fat_out, 1, dir_block_bytes(fp));
         int *status = reinterpret_cast<int *>((char *)long_out + long_field_bytes(g, prec) - 256);
         HISQ_HIP(hipMemsetAsync(status, 0, sizeof(int), s));
-        if (prec == HISQ_F64C)
-            hipLaunchKernelGGL((k_pack_rows<HISQ_F64C, PF64R>), grid, block, 0, s, (const double2 *)long_canon,
-                               (char *)long_out, g, 3, status);
-        else if (prec == HISQ_F32C)
-            hipLaunchKernelGGL((k_pack_rows<HISQ_F32C, PF32R>), grid, block, 0, s, (const double2 *)long_canon,
-                               (char *)long_out, g, 3, status);
-        else
-            hipLaunchKernelGGL((k_pack_rows<HISQ_I16SC, PI16R>), grid, block, 0, s, (const double2 *)long_canon,
-                               (char *)long_out, g, 3, status);
+        hipLaunchKernelGGL((prec == HISQ_F64C   ? k_pack<HISQ_F64C, PF64R>
+                            : prec == HISQ_F32C ? k_pack<HISQ_F32C, PF32R>
+                                                : k_pack<HISQ_I16SC, PI16R>),
+                           grid, block, 0, s, l, g, (const double2 *)long_canon, (char *)long_out, 3, (size_t)0, status);
         HISQ_HIP(hipGetLastError());
         int h_status = 0;
         HISQ_HIP(hipMemcpyAsync(&h_status, status, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -298,18 +286,13 @@ extern "C" int hisq_pack_links(const void *fat_canon, const void *long_canon, co
         if (h_status) return fail(HISQ_EINVAL, "hisq_pack_links: a long link is not +-SU(3) to 1e-6; use an uncompressed precision");
         return HISQ_OK;
     }
-    for (int f = 0; f < 2; ++f) {
-        const double2 *in = (const double2 *)(f ? long_canon : fat_canon);
-        char *out = (char *)(f ? long_out : fat_out);
-        const int hop = f ? 3 : 1;
-        switch (prec) {
-        case HISQ_F64: hipLaunchKernelGGL(k_pack<HISQ_F64>, grid, block, 0, s, in, out, g, hop, bb); break;
-        case HISQ_F32: hipLaunchKernelGGL(k_pack<HISQ_F32>, grid, block, 0, s, in, out, g, hop, bb); break;
-        case HISQ_F16S: hipLaunchKernelGGL(k_pack<HISQ_F16S>, grid, block, 0, s, in, out, g, hop, bb); break;
-        default: hipLaunchKernelGGL(k_pack<HISQ_I16S>, grid, block, 0, s, in, out, g, hop, bb); break;
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "hisq_pack_links launch");
-    }
+    auto kernel = prec == HISQ_F64    ? k_pack<HISQ_F64, void>
+                  : prec == HISQ_F32  ? k_pack<HISQ_F32, void>
+                  : prec == HISQ_F16S ? k_pack<HISQ_F16S, void>
+                                      : k_pack<HISQ_I16S, void>;
+    full(kernel, fat_canon, fat_out, 1, bb);
+    full(kernel, long_canon, long_out, 3, bb);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "hisq_pack_links launch");
     return HISQ_OK;
 }

@@ -152,3 +152,43 @@ def test_fat_paths_coefficients_and_workspaces(hq, dims, coeff):
     with pytest.raises(hq.HisqError) as e:
         hq.hisq_fat_paths(dev(U), coeff, out, dims, torch.empty(3 * field - 16, dtype=torch.uint8, device="cuda"))
     assert e.value.code == hq.HISQ_EWORKSPACE
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 6, 6, 6), (6, 4, 4, 10), (10, 4, 6, 4), (8, 8, 12, 6), (16, 16, 4, 6)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_pack_places_every_matrix(hq, dims):
+    """The FP64 packed field, entry by entry: forward links as they are, backward ones -U^dag from `hop` sites back,
+    zeros in the lanes past the lattice; and the two-row forms hold the same rows."""
+    import torch
+    lx, ly, lz, lt = dims
+    fat, lng = synth.links(dims, 31)
+    V, vh = lx * ly * lz * lt, lx * ly * lz * lt // 2
+    nt = (vh + 63) // 64
+    lex = np.arange(V)
+    c = np.stack([lex % lx, lex // lx % ly, lex // (lx * ly) % lz, lex // (lx * ly * lz)])
+    par = c.sum(0) % 2
+    ref = {}
+    for name, u, hop in (("fat", fat, 1), ("lng", lng, 3)):
+        r = np.zeros((2, nt, 8, 9, 64), np.complex128)
+        for mu in range(4):
+            b = c.copy()
+            b[mu] = (b[mu] - hop) % dims[mu]
+            back = b[0] + lx * (b[1] + ly * (b[2] + lz * b[3]))
+            h = lex >> 1
+            r[par, h >> 6, mu, :, h & 63] = u[mu].reshape(V, 9)
+            r[par, h >> 6, mu + 4, :, h & 63] = -np.conj(np.swapaxes(u[mu][back], 1, 2)).reshape(V, 9)
+        ref[name] = r
+    L = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F64)
+    for name, t in (("fat", L.fat), ("lng", L.lng)):
+        got = t.cpu().numpy().view(np.complex128).reshape(ref[name].shape)
+        assert np.array_equal(got, ref[name]), name
+    C = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F64C)
+    tile = 8 * 6 * 64 * 16 + 64
+    got = C.lng.cpu().numpy()[:2 * nt * tile].reshape(2, nt, tile)
+    rows = np.ascontiguousarray(got[:, :, :-64]).view(np.complex128).reshape(2, nt, 8, 6, 64)
+    assert np.array_equal(rows, ref["lng"][:, :, :, :6])
+    sign = np.ascontiguousarray(got[:, :, -64:]).view(np.uint64)
+    m = np.moveaxis(ref["lng"], 3, 4).reshape(2, nt, 8, 64, 3, 3)
+    neg = np.linalg.det(m).real < 0
+    word = (neg.astype(np.uint64) << np.arange(64, dtype=np.uint64)).sum(-1, dtype=np.uint64)
+    assert np.array_equal(sign, word)
