@@ -386,7 +386,7 @@ __global__ __launch_bounds__(NT) void k_mdslash(Geom g, const char *__restrict__
 // (FP32) or 48 B (FP64) contiguous and a wavefront covers 64 consecutive
 // pairs, so loads are contiguous; per-RHS scalars come from LDS.
 constexpr int MB_NT = 256;
-constexpr int FIN_NT_M = 256;
+constexpr int FIN_NT_M = 1024;
 constexpr int MULTI_MAX_BLOCKS = 2048;
 
 static inline int mblocks(long long pairs)
@@ -667,26 +667,37 @@ __global__ __launch_bounds__(FIN_NT_M) void k_msfinalize(const double *__restric
     __shared__ double lds[FIN_NT_M / 64];
     double acc[1] = { 0.0 };
     strided_sums<FIN_NT_M, 1, 8>(partials, nb, acc);
-    const double v = block_sum<FIN_NT_M>(acc[0], lds);
-    if (threadIdx.x) return;
-    const int n = st->n;
+    __shared__ double total;
+    const double bs = block_sum<FIN_NT_M>(acc[0], lds);
+    if (threadIdx.x == 0) total = bs;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    // one wavefront, lane i for shift i
+    const double v = total;
+    const int i = threadIdx.x;
+    const bool in = i < st->n;
+    const unsigned active = st->active;
+    const bool on = in && (active >> i & 1u);
     switch (mode) {
     case FS_BB:
-        st->bb0 = v;
-        st->rr0 = v;
-        st->stop0 = st->tol2 * v;
-        for (int i = 0; i < n; ++i) st->rr_s[i] = v;
+        if (in) st->rr_s[i] = v;
+        if (i == 0) {
+            st->bb0 = v;
+            st->rr0 = v;
+            st->stop0 = st->tol2 * v;
+        }
         break;
     case FS_PAP: {
         if (!(v > 0.0) || !isfinite(v)) {
-            st->ms_status = HISQ_EBREAKDOWN;
-            st->flags.done = 1;
+            if (i == 0) {
+                st->ms_status = HISQ_EBREAKDOWN;
+                st->flags.done = 1;
+            }
             break;
         }
         const double al = st->rr0 / v;
-        st->alpha0 = al;
-        for (int i = 0; i < n; ++i) {
-            if (!(st->active & (1u << i))) continue;
+        if (i == 0) st->alpha0 = al;
+        if (on) {
             const double z = st->zeta[i], zp = st->zeta_prev[i];
             const double den = zp * st->a_prev * (1.0 + al * st->dsig[i]) + al * st->b_prev * (zp - z);
             const double zn = z * zp * st->a_prev / den;
@@ -696,28 +707,36 @@ __global__ __launch_bounds__(FIN_NT_M) void k_msfinalize(const double *__restric
         break;
     }
     case FS_UPD: {
-        st->iter += 1;
         if (!isfinite(v)) {
-            st->ms_status = HISQ_EBREAKDOWN;
-            st->flags.done = 1;
+            if (i == 0) {
+                st->iter += 1;
+                st->ms_status = HISQ_EBREAKDOWN;
+                st->flags.done = 1;
+            }
             break;
         }
         const double be = v / st->rr0;
-        st->beta0 = be;
-        for (int i = 0; i < n; ++i) {
-            if (!(st->active & (1u << i))) continue;
+        bool drop = false;
+        if (on) {
             st->iters[i] += 1;
-            const double q = st->zeta_next[i] / st->zeta[i];
+            const double z = st->zeta[i], zn = st->zeta_next[i], q = zn / z;
             st->beta_s[i] = be * q * q;
-            st->zeta_prev[i] = st->zeta[i];
-            st->zeta[i] = st->zeta_next[i];
-            st->rr_s[i] = st->zeta[i] * st->zeta[i] * v;
-            if (st->rr_s[i] <= st->stop0) st->active &= ~(1u << i);
+            st->zeta_prev[i] = z;
+            st->zeta[i] = zn;
+            const double rs = zn * zn * v;
+            st->rr_s[i] = rs;
+            drop = rs <= st->stop0;
         }
-        st->a_prev = st->alpha0;
-        st->b_prev = be;
-        st->rr0 = v;
-        if (!st->active) st->flags.done = 1;
+        const unsigned left = active & ~(unsigned)__ballot(drop);
+        if (i == 0) {
+            st->iter += 1;
+            st->beta0 = be;
+            st->a_prev = st->alpha0;
+            st->b_prev = be;
+            st->rr0 = v;
+            st->active = left;
+            if (!left) st->flags.done = 1;
+        }
         break;
     }
     }
@@ -856,123 +875,132 @@ enum {
     FM_FINAL = 5,     // rr_true of every RHS (final check)
 };
 
-__device__ void mfinalize(MultiState *st, int mode, const double *v)
+// One wavefront, lane r for right-hand side r: the N chains of loads and FP64
+// divisions run side by side instead of one after the other.
+__device__ __forceinline__ void mfinalize(MultiState *st, int mode, const double *v)
 {
-    const int n = st->n;
+    const int n = st->n, r = threadIdx.x & 63;
+    const bool in = r < n;
+    const unsigned bit = in ? 1u << r : 0u, active = st->active, relmask = st->relmask;
+    const double x = in ? v[r] : 0.0;
+    bool drop = false, rel = false;  // RHS r leaves the active set / asks for a reliable update
     switch (mode) {
     case FM_BB:
-        for (int r = 0; r < n; ++r) { st->bb[r] = v[r]; st->stop2[r] = st->tol2 * v[r]; }
+        if (in) {
+            st->bb[r] = x;
+            st->stop2[r] = st->tol2 * x;
+        }
         break;
     case FM_INIT: {
-        unsigned act = 0;
-        for (int r = 0; r < n; ++r) {
-            st->rr[r] = st->rr_true[r] = st->maxrr[r] = v[r];
-            if (st->bb[r] > 0.0 && v[r] > st->stop2[r]) act |= 1u << r;
+        bool on = false;
+        if (in) {
+            st->rr[r] = st->rr_true[r] = st->maxrr[r] = x;
+            on = st->bb[r] > 0.0 && x > st->stop2[r];
         }
-        st->active = act;
-        st->relmask = 0;
-        st->flags.reliable = 0;
-        st->flags.done = act == 0;
+        const unsigned act = (unsigned)__ballot(on);
+        if (r == 0) {
+            st->active = act;
+            st->relmask = 0;
+            st->flags.reliable = 0;
+            st->flags.done = act == 0;
+        }
         break;
     }
     case FM_PAP:
-        for (int r = 0; r < n; ++r) {
-            if (!(st->active & (1u << r))) continue;
-            if (!(v[r] > 0.0) || !isfinite(v[r])) {
-                st->status[r] = HISQ_EBREAKDOWN;
-                st->active &= ~(1u << r);
-                st->alpha[r] = 0.0;
-            } else {
-                st->alpha[r] = st->rr[r] / v[r];
-            }
-        }
-        if (!st->active) st->flags.done = 1;
-        break;
     case FM_UPD:
-        st->iter += 1;
-        for (int r = 0; r < n; ++r) {
-            if (!(st->active & (1u << r))) continue;
-            st->iters[r] += 1;
-            const double x = v[r];
-            if (!isfinite(x)) {
+        if (active & bit) {
+            if (mode == FM_UPD) st->iters[r] += 1;
+            drop = mode == FM_PAP ? !(x > 0.0) || !isfinite(x) : !isfinite(x);
+            if (drop) {
                 st->status[r] = HISQ_EBREAKDOWN;
-                st->active &= ~(1u << r);
+                if (mode == FM_PAP) st->alpha[r] = 0.0;
+            } else if (mode == FM_PAP) {
+                st->alpha[r] = st->rr[r] / x;
             } else {
                 // a reliable update is due: flag it for the end of the captured
                 // iterations and keep iterating (the batch is not paused)
-                if (x <= st->stop2[r] || x < st->delta2 * st->maxrr[r]) st->relmask |= 1u << r;
+                rel = x <= st->stop2[r] || x < st->delta2 * st->maxrr[r];
                 st->maxrr[r] = fmax(st->maxrr[r], x);
                 st->beta[r] = x / st->rr[r];
                 st->rr[r] = x;
             }
         }
-        if (!st->active) st->flags.done = 1;
         break;
     case FM_RELIABLE:
-        for (int r = 0; r < n; ++r) {
-            if (!(st->relmask & (1u << r))) continue;
-            const double x = v[r];
+        if (relmask & bit) {
             st->rr_true[r] = x;
             st->nupd[r] += 1;
             st->beta[r] = x / st->rr[r];
             st->rr[r] = x;
             st->maxrr[r] = x;
-            if (!isfinite(x)) {
-                st->status[r] = HISQ_EBREAKDOWN;
-                st->active &= ~(1u << r);
-            } else if (x <= st->stop2[r]) {
-                st->status[r] = HISQ_OK;
-                st->active &= ~(1u << r);
-            }
+            drop = !isfinite(x) || x <= st->stop2[r];
+            if (drop) st->status[r] = isfinite(x) ? HISQ_OK : HISQ_EBREAKDOWN;
         }
-        st->relmask = 0;
-        st->flags.reliable = 0;
-        if (!st->active) st->flags.done = 1;
         break;
     case FM_FINAL:
-        for (int r = 0; r < n; ++r) st->rr_true[r] = v[r];
+        if (in) st->rr_true[r] = x;
         break;
     }
-}
-
-// Column sums of red[FIN_NT_M][N] into tot[N]: wave w takes columns w, w + 4,
-// ..., each lane adds 4 rows and a butterfly finishes (fixed order).
-template <int N>
-__device__ __forceinline__ void column_sums(const double *red, double *tot)
-{
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    for (int r = w; r < N; r += FIN_NT_M / 64) {
-        double v = 0.0;
-        for (int t = l; t < FIN_NT_M; t += 64) v += red[t * N + r];
-        v = wave_sum(v);
-        if (l == 0) tot[r] = v;
+    if (mode != FM_PAP && mode != FM_UPD && mode != FM_RELIABLE) return;
+    const unsigned left = active & ~(unsigned)__ballot(drop), asked = relmask | (unsigned)__ballot(rel);
+    if (r == 0) {
+        st->active = left;
+        if (mode == FM_UPD) {
+            st->iter += 1;
+            st->relmask = asked;
+        }
+        if (mode == FM_RELIABLE) {
+            st->relmask = 0;
+            st->flags.reliable = 0;
+        }
+        if (!left) st->flags.done = 1;
     }
 }
 
-// Rows of partials [nblocks][N] a finaliser thread loads before adding any:
-// 16 loads in flight per thread whatever N is.
-template <int N> constexpr int fin_rows() { return N >= 16 ? 1 : 16 / N; }
+// tot[c] = sum over the rows of partials [nrows][N], in a fixed order: thread t
+// takes column t % N of the rows t / N, t / N + FIN_NT_M / N, ... (consecutive
+// threads on consecutive doubles, 8 loads in flight each), the lanes of a
+// wavefront meet by butterflies, the wavefronts in LDS.  One workgroup does
+// this between two Dslashes, so its latency counts in full: 1024 threads
+// against 256 with a whole row each.  24^4, N = 8, with the lane-parallel
+// mfinalize: the kernel of <p, A p> (two sums) 11.2 -> 6.6 us, that of |r|^2
+// 10.1 -> 4.9 us.  Every thread calls it; red holds FIN_NT_M / 64 * N.
+template <int N>
+__device__ __forceinline__ void column_totals(const double *__restrict__ p, int nrows, double *red, double *tot)
+{
+    constexpr int U = 8;
+    const int n = nrows * N;
+    double acc = 0.0;
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * FIN_NT_M) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = i0 + u * FIN_NT_M < n ? p[i0 + u * FIN_NT_M] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += v[u];
+    }
+#pragma unroll
+    for (int o = 32; o >= N; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (l < N) red[w * N + l] = acc;
+    __syncthreads();
+    if (threadIdx.x < N) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < FIN_NT_M / 64; ++k) s += red[k * N + threadIdx.x];
+        tot[threadIdx.x] = s;
+    }
+    __syncthreads();
+}
 
-// One pass over the [nblocks][N] partials: thread i keeps the N sums of
-// blocks i, i + 256, ... in registers, then the 256 x N sums are added
-// column by column.
 template <int N>
 __global__ __launch_bounds__(FIN_NT_M) void k_mfinalize(const double *__restrict__ partials, int nblocks,
                                                         MultiState *st, int mode, int gate)
 {
     if (solver_gate_closed(&st->flags, gate)) return;  // first: paused iterations stay cheap
-    __shared__ double red[FIN_NT_M * N];
+    __shared__ double red[FIN_NT_M / 64 * N];
     __shared__ double tot[N];
-    double acc[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) acc[r] = 0.0;
-    strided_sums<FIN_NT_M, N, fin_rows<N>()>(partials, nblocks, acc);
-#pragma unroll
-    for (int r = 0; r < N; ++r) red[threadIdx.x * N + r] = acc[r];
-    __syncthreads();
-    column_sums<N>(red, tot);
-    __syncthreads();
-    if (threadIdx.x == 0) mfinalize(st, mode, tot);
+    column_totals<N>(partials, nblocks, red, tot);
+    if (threadIdx.x < 64) mfinalize(st, mode, tot);
 }
 
 // <p_r, A p_r> = m4_r |p_r|^2 + |D_oe p_r|^2 (D_eo = -D_oe^dag) from the partials of
@@ -982,30 +1010,13 @@ __global__ __launch_bounds__(FIN_NT_M) void k_mfinalize_pap(const double *__rest
                                                             const double *__restrict__ part_p, int npp, MultiState *st)
 {
     if (paused(st->flags)) return;
-    __shared__ double red[FIN_NT_M * N];
-    __shared__ double tot[N];
-    double acc[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) acc[r] = 0.0;
-    strided_sums<FIN_NT_M, N, fin_rows<N>()>(part_t, ntt, acc);
-    double accp[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) accp[r] = 0.0;
-    strided_sums<FIN_NT_M, N, fin_rows<N>()>(part_p, npp, accp);
-    __shared__ double tt[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) red[threadIdx.x * N + r] = acc[r];
-    __syncthreads();
-    column_sums<N>(red, tt);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < N; ++r) red[threadIdx.x * N + r] = accp[r];
-    __syncthreads();
-    column_sums<N>(red, tot);
-    __syncthreads();
+    __shared__ double red[FIN_NT_M / 64 * N], redp[FIN_NT_M / 64 * N];
+    __shared__ double tt[N], tot[N];
+    column_totals<N>(part_t, ntt, red, tt);
+    column_totals<N>(part_p, npp, redp, tot);
     if (threadIdx.x < N) tot[threadIdx.x] = fma(st->m4[threadIdx.x], tot[threadIdx.x], tt[threadIdx.x]);
     __syncthreads();
-    if (threadIdx.x == 0) mfinalize(st, FM_PAP, tot);
+    if (threadIdx.x < 64) mfinalize(st, FM_PAP, tot);
 }
 
 __global__ void k_mstate_init(MultiState *st, int n, double tol2, double delta2, const double *m4)
@@ -1083,7 +1094,26 @@ static const MShape MSHAPES[N_MSHAPES] = { { 1, 256, 0, 0 }, { 2, 256, 0, 0 }, {
                                            { 4, 256, 0, 1 }, { 4, 256, 1, 1 }, { 2, 256, 1, 1 }, { 4, 256, 1, 3 },
                                            { 2, 256, 1, 3 }, { 4, 256, 1, 4 }, { 2, 256, 1, 4 }, { 4, 256, 1, 5 } };
 
-template <class PS> static int mshape_for(const Geom &g, int N) { return tuned_choice("mdslash", g, PS::prec, N, 0); }
+// Untuned choice, from the times of every shape (us; one RHS group per site
+// and 256 threads, this): N = 1 32^4 111, 102; N = 2 16^4 18.0, 17.4; N = 4
+// 8^4 15.1, 9.9, 16^4 21.8, 17.7, 32^4 147, 140; N = 8 16^4 31.7, 19.5, 24^4
+// 85, 76, 32^4 231, 214; N = 16 8^4 47.2, 15.5, 16^4 58, 27, 32^4 476, 382.
+// Four threads per site (2: loads as they are needed; 4: issued a direction
+// ahead) fill the chip on few tiles, and keep N = 16 in registers.
+static int default_mshape(const Geom &g, int N)
+{
+    switch (N) {
+    case 1: return 3;
+    case 2: return g.ntiles <= 2048 ? 3 : 0;
+    case 4: return g.ntiles <= 64 ? 2 : g.ntiles <= 4096 ? 1 : 5;
+    case 8: return g.ntiles <= 1280 ? 2 : 4;
+    default: return g.ntiles <= 64 ? 2 : 4;
+    }
+}
+template <class PS> static int mshape_for(const Geom &g, int N)
+{
+    return tuned_choice("mdslash", g, PS::prec, N, default_mshape(g, N));
+}
 
 // Link storage of the batched solvers: the outer FP64 links (reliable
 // updates, true residuals) and the inner FP32 links, both full or both with
