@@ -193,20 +193,82 @@ __global__ __launch_bounds__(BL_NT) void k_dot_state(const T *__restrict__ x, co
     block_partial<BL_NT>(s, partials, blockIdx.x);
 }
 
-// p = r + beta p ; partials of |p|^2 (the first half of the next <p, A p>)
-template <class T>
-__global__ __launch_bounds__(BL_NT) void k_cg_p_norm(T *__restrict__ p, const T *__restrict__ r, long long n,
-                                                     double *partials, const CGState *st)
+// Sum over the workgroup of the wavefronts' sums w, to every thread, in a fixed order.
+template <int NT> __device__ __forceinline__ double fold_total(double w, double *lds)
 {
-    if (paused(st->flags)) return;
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = w;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) s += lds[i];
+    return s;
+}
+
+// The |r|^2 of the folded iteration: k_cg_p_norm and k_fold_settle add the
+// partials in the same order, so a solve does not depend on its pauses.
+__device__ __forceinline__ double fold_rr(const double *__restrict__ part, int n, double *lds)
+{
+    double rr[1] = { 0.0 };
+    strided_sums<BL_NT, 1, 8>(part, n, rr);
+    return fold_total<BL_NT>(wave_sum_dpp(rr[0]), lds);
+}
+
+// The last iteration's |r|^2 into the state, before the host reads it.
+__global__ __launch_bounds__(BL_NT) void k_fold_settle(const double *__restrict__ part, int n, CGState *st, int mode)
+{
+    __shared__ double lds[BL_NT / 64];
+    if (paused(st->flags) || !st->pending) return;
+    const double v = fold_rr(part, n, lds);
+    if (threadIdx.x == 0) {
+        st->pending = 0;
+        finalize(st, mode, v);
+    }
+}
+
+// What a FOLD kernel takes over from the one-workgroup finaliser before it:
+// the partials of the reductions, and the copy of the state that one thread
+// writes while all read the other (see FoldIter).
+struct Fold {
+    const double *a, *b;
+    int na, nb, mode;
+    CGState *out;
+};
+
+// p = r + beta p ; partials of |p|^2 (the first half of the next <p, A p>).
+// FOLD: finishes the previous iteration from its |r|^2 partials f.a first; the
+// sums run while p and r are in flight.
+template <class T, bool FOLD>
+__global__ __launch_bounds__(BL_NT) void k_cg_p_norm(T *__restrict__ p, const T *__restrict__ r, long long n,
+                                                     double *partials, const CGState *st, Fold f)
+{
+    const bool lead = FOLD && blockIdx.x == 0 && threadIdx.x == 0;
+    if (paused(st->flags)) {
+        if (lead) *f.out = *st;
+        return;
+    }
     using R = typename VecT<T>::real;
-    const R beta = (R)st->beta;
     T pv[BL_U], rv[BL_U];
 #pragma unroll
     for (int j = 0; j < BL_U; ++j) {
         const long long i = bl_index(j);
         if (i < n) { pv[j] = p[i]; rv[j] = r[i]; }
     }
+    double bt;
+    if constexpr (FOLD) {
+        __shared__ double lds[BL_NT / 64];
+        CGState c = *st;
+        const double total = fold_rr(f.a, f.na, lds);
+        if (c.pending) {
+            c.pending = 0;
+            finalize(&c, f.mode, total);
+        }
+        if (lead) *f.out = c;
+        if (paused(c.flags)) return;
+        bt = c.beta;
+    } else {
+        bt = st->beta;
+    }
+    const R beta = (R)bt;
     double s = 0.0;
 #pragma unroll
     for (int j = 0; j < BL_U; ++j) {
@@ -357,31 +419,63 @@ __global__ __launch_bounds__(NT) HISQ_WAVES(W) void k_cg_Dp(Geom g, const char *
     block_partial<NT>(s, partials, blk);
 }
 
-// A p = m4 p - D_eo t in registers ; x += alpha p ; r -= alpha A p ; partials of |r|^2
-template <class P, int NT, int W>
+// A p = m4 p - D_eo t in registers ; x += alpha p ; r -= alpha A p ; partials
+// of |r|^2.  FOLD: alpha from the |t|^2 (f.a) and |p|^2 (f.b) partials; each
+// wavefront sums its share before the Dslash, the shares meet after it.
+template <class P, int NT, int W, bool FOLD>
 __global__ __launch_bounds__(NT) HISQ_WAVES(W) void k_cg_Ap_upd(Geom g, const char *__restrict__ fat,
                                                                 const char *__restrict__ lng,
                                                                 const typename P::cvec *__restrict__ t,
                                                                 const typename P::cvec *__restrict__ p,
                                                                 typename P::cvec *__restrict__ x,
                                                                 typename P::cvec *__restrict__ r, int nblocks,
-                                                                double *partials, const CGState *st)
+                                                                double *partials, const CGState *st, Fold f)
 {
-    if (paused(st->flags)) return;
+    const bool lead = FOLD && blockIdx.x == 0 && threadIdx.x == 0;
+    if (paused(st->flags)) {
+        if (lead) *f.out = *st;
+        return;
+    }
     const int blk = xcd_block(blockIdx.x, gridDim.x);
-    if (blk >= nblocks) return;
+    if (blk >= nblocks) return;  // workgroup 0 has block 0
+    __shared__ double lds[FOLD ? NT / 64 : 1];
+    if constexpr (FOLD) {
+        double tt[1] = { 0.0 }, pp[1] = { 0.0 };
+        strided_sums<NT, 1, 8>(f.a, f.na, tt);
+        strided_sums<NT, 1, 8>(f.b, f.nb, pp);
+        const double w = wave_sum_dpp(fma(st->m4, pp[0], tt[0]));
+        if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = w;
+    }
     const int k = blk * (NT / TILE) + (threadIdx.x >> 6);
     const int tile = k < g.ntiles ? tile_of(g, k) : 0;
     const int lane = threadIdx.x & 63;
     const int h = tile * TILE + lane;
     double s = 0.0;
+    typename P::real acc[6];
     if (k < g.ntiles) {
         const int hc = h < g.Vh ? h : g.Vh - 1;
-        typename P::real acc[6];
         dslash_site<P, cg_unroll<P>()>(g, fat, lng, t, 0, tile, lane, hc, acc);
+    }
+    double alpha;
+    if constexpr (FOLD) {
+        __syncthreads();
+        double pap = 0.0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) pap += lds[i];
+        if (lead) {
+            *f.out = *st;
+            finalize(f.out, FIN_PAP, pap);
+            f.out->pending = f.out->flags.done ? 0 : 1;
+        }
+        if (!(pap > 0.0) || !isfinite(pap)) return;  // as FIN_PAP decides
+        alpha = st->rr / pap;
+    } else {
+        alpha = st->alpha;
+    }
+    if (k < g.ntiles) {
         if (h < g.Vh) {
             using R = typename P::real;
-            const R m = (R)st->m4, a = (R)st->alpha;
+            const R m = (R)st->m4, a = (R)alpha;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const size_t i = (size_t)h * 3 + c;
@@ -688,9 +782,9 @@ struct Launch {
     {
         using V = typename P::cvec;
         if (e0) hipEventRecord(e0, q);
-        hipLaunchKernelGGL((k_cg_Ap_upd<P, CG_NT, cg_waves<P>()>), gd, dim3(CG_NT), 0, q, g, (const char *)fat,
+        hipLaunchKernelGGL((k_cg_Ap_upd<P, CG_NT, cg_waves<P>(), false>), gd, dim3(CG_NT), 0, q, g, (const char *)fat,
                            (const char *)lng, (const V *)t, (const V *)p, (V *)x, (V *)r, nbd, part,
-                           (const CGState *)st);
+                           (const CGState *)st, Fold{});
         if (e1) hipEventRecord(e1, q);
         fin(q, nbd, mode, GATE_PAUSE);
     }
@@ -698,8 +792,65 @@ struct Launch {
     template <class T> void pupd(hipStream_t q, T *p, const T *r, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) const
     {
         if (e0) hipEventRecord(e0, q);
-        hipLaunchKernelGGL((k_cg_p_norm<T>), gb, dim3(BL_NT), 0, q, p, r, n, part_p, (const CGState *)st);
+        hipLaunchKernelGGL((k_cg_p_norm<T, false>), gb, dim3(BL_NT), 0, q, p, r, n, part_p, (const CGState *)st,
+                           Fold{});
         if (e1) hipEventRecord(e1, q);
+    }
+};
+
+// The iteration of the lattices between the split form and the largest: the
+// three kernels above without the two finalisers, p = r + beta p (finishing
+// the previous iteration), t = D_oe p, the update.  The states alternate as in
+// SplitIter: k_cg_p_norm st -> s1, k_cg_Ap_upd s1 -> st.
+struct FoldIter {
+    bool on = false;
+    CGState *s1 = nullptr;
+    double *part_t = nullptr, *part_p = nullptr, *part_r = nullptr;
+    // `scratch` as in SplitIter::set
+    void set(const Launch &L, int prec, void *scratch, size_t bytes)
+    {
+        const size_t head = (sizeof(CGState) + 63) & ~(size_t)63;
+        on = fold_pays(L.g, prec) && head + (2 * (size_t)L.nbd + L.nbl) * sizeof(double) <= bytes;
+        s1 = (CGState *)scratch;
+        part_t = (double *)((char *)scratch + head);
+        part_p = part_t + L.nbd;
+        part_r = part_p + L.nbl;
+    }
+    // Microseconds per iteration of a whole solve (its reliable updates
+    // included, mass 0.08), five kernels and these three:
+    //                          FP64          FP32          16-bit two rows
+    //   20^4 (1250 tiles)      103.5 100.4   (split form)
+    //   24^4 (2592)            166.1 164.4   98.1  92.7    82.9  78.2
+    //   24^2 x 28^2 (3528)     222.2 222.1   124.9 120.1   103.6 99.3
+    //   28^4 (4802)            297.2 300.6   162.9 158.7   132.2 127.4
+    //   32^4 (8192)            470.0 482.8   267.4 264.4   204.0 200.8
+    //   36^4 (13122)           754.5 753.8   430.0 430.9   319.9 320.2
+    // The launches saved are a fixed few microseconds, while all workgroups
+    // together read a volume of partials that grows with the square of the
+    // lattice.  FP64 loses earlier than the rest; why was not separated.
+    static bool fold_pays(const Geom &g, int prec)
+    {
+        return g.ntiles <= (prec == HISQ_F64 || prec == HISQ_F64C ? 3072 : 8192);
+    }
+    template <class P>
+    hipError_t iteration(hipStream_t q, const Launch &L, const void *fat, const void *lng, void *r, void *p, void *t,
+                         void *x, int mode) const
+    {
+        using V = typename P::cvec;
+        hipLaunchKernelGGL((k_cg_p_norm<V, true>), L.gb, dim3(BL_NT), 0, q, (V *)p, (const V *)r, L.n, part_p,
+                           (const CGState *)L.st, (Fold{ part_r, nullptr, L.nbd, 0, mode, s1 }));
+        hipLaunchKernelGGL((k_cg_Dp<P, CG_NT, cg_waves<P>()>), L.gd, dim3(CG_NT), 0, q, L.g, (const char *)fat,
+                           (const char *)lng, (const V *)p, (V *)t, L.nbd, part_t, (const CGState *)s1);
+        hipLaunchKernelGGL((k_cg_Ap_upd<P, CG_NT, cg_waves<P>(), true>), L.gd, dim3(CG_NT), 0, q, L.g,
+                           (const char *)fat, (const char *)lng, (const V *)t, (const V *)p, (V *)x, (V *)r, L.nbd,
+                           part_r, (const CGState *)s1, (Fold{ part_t, part_p, L.nbd, L.nbl, FIN_PAP, L.st }));
+        return hipGetLastError();
+    }
+    hipError_t settle(hipStream_t q, const Launch &L, int mode) const
+    {
+        if (!on) return hipSuccess;
+        hipLaunchKernelGGL(k_fold_settle, dim3(1), dim3(BL_NT), 0, q, (const double *)part_r, L.nbd, L.st, mode);
+        return hipGetLastError();
     }
 };
 
@@ -814,11 +965,18 @@ int cg_plain(double mass, double tol, const void *fat, const void *lng, const vo
 
     // timing mode keeps the three kernels it reports
     SplitIter sp;
-    if (o.use_graph != 2) sp.set(g, PH::prec, st, (char *)(st + 1), (size_t)((char *)r - (char *)(st + 1)));
+    FoldIter fo;
+    if (o.use_graph != 2) {
+        char *scratch = (char *)(st + 1);
+        const size_t bytes = (size_t)((char *)r - scratch);
+        sp.set(g, PH::prec, st, scratch, bytes);
+        if (!sp.on) fo.set(L, PH::prec, scratch, bytes);
+    }
     IterTimer tm;
     if (o.use_graph == 2 && !tm.start(o.check_every)) return fail(HISQ_EHIP, "cg_solve: event creation failed");
     auto iter = [&](hipStream_t q) -> hipError_t {
         if (sp.on) return sp.template iteration<PH>(q, g, fat, lng, r, p, t, x, FIN_UPD_PLAIN);
+        if (fo.on) return fo.template iteration<PH>(q, L, fat, lng, r, p, t, x, FIN_UPD_PLAIN);
         L.dp<PH>(q, fat, lng, p, t, tm.at(0), tm.at(1));
         L.ap_update<PH>(q, fat, lng, t, p, x, r, FIN_UPD_PLAIN, tm.at(2), tm.at(3));
         L.pupd<double2>(q, p, r, tm.at(4), tm.at(5));
@@ -826,7 +984,9 @@ int cg_plain(double mass, double tol, const void *fat, const void *lng, const vo
         return hipGetLastError();
     };
     auto on_check = [&](int ran) { if (tm.K) tm.collect(ran); };
-    auto settle = [&](hipStream_t q) { return sp.settle(q, g, FIN_UPD_PLAIN); };
+    auto settle = [&](hipStream_t q) {
+        return fo.on ? fo.settle(q, L, FIN_UPD_PLAIN) : sp.settle(q, g, FIN_UPD_PLAIN);
+    };
 
     int restarts = 0;
     int status = HISQ_OK;
@@ -913,10 +1073,15 @@ int cg_mixed(double mass, double tol, const void *fat, const void *lng, const vo
     const dim3 gb(L.nbl), bb(BL_NT);
     SplitIter sp;  // its scratch: t64, which only the reliable update uses
     sp.set(g, PS::prec, st, t64, v64);
-    auto settle = [&](hipStream_t q) { return sp.settle(q, g, FIN_UPD_MIXED); };
+    FoldIter fo;
+    if (!sp.on) fo.set(L, PS::prec, t64, v64);
+    auto settle = [&](hipStream_t q) {
+        return fo.on ? fo.settle(q, L, FIN_UPD_MIXED) : sp.settle(q, g, FIN_UPD_MIXED);
+    };
     // one inner iteration; a reliable update request pauses the rest of the graph
     auto iter = [&](hipStream_t q) -> hipError_t {
         if (sp.on) return sp.template iteration<PS>(q, g, fat_lo, lng_lo, rs, ps, ts, xs, FIN_UPD_MIXED);
+        if (fo.on) return fo.template iteration<PS>(q, L, fat_lo, lng_lo, rs, ps, ts, xs, FIN_UPD_MIXED);
         L.dp<PS>(q, fat_lo, lng_lo, ps, ts);
         L.ap_update<PS>(q, fat_lo, lng_lo, ts, ps, xs, rs, FIN_UPD_MIXED);
         L.pupd<float2>(q, ps, rs);
@@ -928,7 +1093,7 @@ int cg_mixed(double mass, double tol, const void *fat, const void *lng, const vo
         hipError_t e = launch_dslash<PH>(g, fat, lng, x, t64, 1, q, &st->flags, GATE_RELIABLE);
         if (e != hipSuccess) return e;
         L.template resid<PH>(q, fat, lng, t64, x, b, r64, nullptr, rs, nullptr, FIN_RELIABLE, GATE_RELIABLE);
-        if (!sp.on) L.pupd<float2>(q, ps, rs);  // the split iteration takes r + beta p itself
+        if (!sp.on && !fo.on) L.pupd<float2>(q, ps, rs);  // the other forms take r + beta p themselves
         return hipGetLastError();
     };
 

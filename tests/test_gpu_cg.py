@@ -183,8 +183,8 @@ def test_cg_blocked_tile_order(hq, mode):
     assert abs(s1["iters"] - s0["iters"]) <= 3
 
 
-# two kernels per iteration up to 768 tiles, three up to 1280 (FP64: while the partials fit beside the state), five
-# beyond; 6^4 and 6x4x4x10 have ragged tiles
+# two kernels per iteration up to 768 tiles, three up to 1280 (FP64: while the partials fit beside the state), then
+# three of another kind up to 3072 (FP64 vectors) or 8192; 6^4 and 6x4x4x10 have ragged tiles
 @pytest.mark.parametrize("mode", [0, 1, 4, 6])
 @pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 4, 10), (6, 6, 6, 6), (16, 16, 16, 24), (14, 14, 18, 28),
                                   (20, 16, 16, 32), (18, 18, 22, 24)], ids=lambda d: "x".join(map(str, d)))
@@ -201,3 +201,18 @@ def test_cg_kernel_forms(hq, dims, mode):
     for kw in (dict(use_graph=0), dict(check_every=7)):
         y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, **kw)
         assert s2["iters"] == st["iters"] and np.array_equal(x, y)
+
+
+# the last lattice without finalisers of their own and one beyond it, per type of the vectors
+@pytest.mark.parametrize("dims,mode", [((24, 24, 24, 28), 0), ((24, 24, 28, 28), 0), ((32, 32, 32, 32), 1),
+                                       ((32, 32, 32, 34), 1)])
+def test_cg_folded_line(hq, dims, mode):
+    mass = 0.2
+    fat, lng = fields(dims, synth.gauge_seed(15))
+    b = synth.source(dims, synth.source_seed(15))
+    x, st = _solve(hq, dims, fat, lng, b, mass, mode)
+    tr = oracle.true_residual(dims, mass, fat, lng, b, x)
+    say(f"cg folded line {dims} mode={mode}: iters={st['iters']} oracle_resid={tr:.3e}")
+    assert st["rc"] == 0 and tr <= CG_TOL and st["fallback_used"] == 0
+    y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, check_every=7)
+    assert s2["iters"] == st["iters"] and np.array_equal(x, y)
