@@ -21,6 +21,7 @@
 #include <cstring>
 
 #include "cg_internal.hpp"
+#include "split_sums.hpp"
 
 namespace hisq {
 
@@ -39,6 +40,7 @@ struct FState {
     int window_start;   // iteration at which the current progress window opened
     double m4, bb, stop2, rr, best_rr, zr, zr_old, zrp, pAp, alpha, beta, rr_true;
     double rr_window;   // lowest |r|^2 when the window opened
+    int pending;        // four-kernel form: the last iteration's |r|^2 partials are not in the state yet
 };
 // progress rule: over every FCG_WINDOW iterations the lowest |r| reached must
 // fall below half the lowest before the window (|r|^2 / 4), otherwise the
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(F_NT) void k_f_p(double2 *__restrict__ p, const dou
     for (int j = 0; j < F_U; ++j) {
         const long long i = f_index(j);
         if (i < n) {
-            double2 pv = p[i];
+            double2 pv = st->iter ? p[i] : make_double2(0.0, 0.0);  // not written before the first direction
             const double2 zv = z[i];
             pv.x = fma(be, pv.x, zv.x);
             pv.y = fma(be, pv.y, zv.y);
@@ -211,17 +213,8 @@ __global__ __launch_bounds__(256) HISQ_WAVES(8) void k_f_resid(Geom g, const cha
 
 enum { FF_BB = 0, FF_INIT = 1, FF_Z = 2, FF_PAP = 3, FF_UPD = 4, FF_TRUE = 5 };
 
-__global__ __launch_bounds__(256) void k_f_fin(const double *__restrict__ partials, int nb, int pairs, FState *st,
-                                               int mode)
+__device__ __forceinline__ void f_finalize(FState *st, int mode, double a, double b)
 {
-    if (st->flags.done && (mode == FF_Z || mode == FF_PAP || mode == FF_UPD)) return;
-    __shared__ double lds[2 * 4];
-    double acc[2] = { 0.0, 0.0 };
-    if (pairs) strided_sums<256, 2, 4>(partials, nb, acc);
-    else strided_sums<256, 1, 8>(partials, nb, acc);
-    double a = acc[0], b = acc[1];
-    block_sum2<256>(a, b, lds);
-    if (threadIdx.x) return;
     switch (mode) {
     case FF_BB: st->bb = a; st->stop2 = st->stop2 * a; break;  // stop2 holds tol^2 until here
     case FF_INIT:
@@ -258,12 +251,234 @@ __global__ __launch_bounds__(256) void k_f_fin(const double *__restrict__ partia
     }
 }
 
+__global__ __launch_bounds__(256) void k_f_fin(const double *__restrict__ partials, int nb, int pairs, FState *st,
+                                               int mode)
+{
+    if (st->flags.done && (mode == FF_Z || mode == FF_PAP || mode == FF_UPD)) return;
+    __shared__ double lds[2 * 4];
+    double acc[2] = { 0.0, 0.0 };
+    if (pairs) strided_sums<256, 2, 4>(partials, nb, acc);
+    else strided_sums<256, 1, 8>(partials, nb, acc);
+    double a = acc[0], b = acc[1];
+    block_sum2<256>(a, b, lds);
+    if (threadIdx.x == 0) f_finalize(st, mode, a, b);
+}
+
+// The iteration on small lattices: four kernels, each finishing the reduction
+// of the one before it (every workgroup reads all partials, in one order), and
+// the two Dslashes with a workgroup per 64-site tile.  The state goes round
+// three copies, s0 -k_fs_z-> s1 -k_fs_p-> s2 -k_fs_upd-> s0, written by one
+// thread, so no workgroup reads what another writes.  <p, A p> is
+// 4 m^2 |p|^2 + |D_oe p|^2.
+// Such an iteration is launches and latency: at 16^4 the eight kernels took
+// 66 us beside 43 us of network, 24 of them the second Dslash with one
+// wavefront per tile, 14 the three one-workgroup finalisers.  These four take
+// 13 and 15 us (Dslashes) and 4.7 each.  A whole
+// solve with 4 channels at mass 0.06, eight kernels and these four, ms:
+//   8^4 7.73 4.95;  12^4 9.30 6.04;  16^4 12.6 10.1;  16^3 x 24 15.7 15.0
+// (16^4, mass 0.02: 37.1, 29.8).  The line is that of the split Dslash,
+// 768 tiles (16^3 x 24), where the gain runs out.
+
+// |r|^2 of the last iteration; k_fs_z and k_fs_settle add in the same order.
+__device__ __forceinline__ double fs_rr(const double *__restrict__ part, int n, double *lds)
+{
+    double rr[1] = { 0.0 };
+    strided_sums<SPLIT_NT, 1, 2>(part, n, rr);
+    return split_total(rr[0], lds);
+}
+
+// partials of Re<z, r> and Re<z, r_prev>; finishes the previous iteration
+__global__ __launch_bounds__(SPLIT_NT) void k_fs_z(const float2 *__restrict__ z, const double2 *__restrict__ r,
+                                                   const double2 *__restrict__ rp, long long n,
+                                                   const double *__restrict__ part_rr, int ntiles,
+                                                   double *__restrict__ part_z, const FState *__restrict__ s0,
+                                                   FState *__restrict__ s1)
+{
+    __shared__ double lds[SPLIT], lda[SPLIT], ldb[SPLIT];
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    if (s0->flags.done) {
+        if (lead) *s1 = *s0;
+        return;
+    }
+    const bool pending = s0->pending;
+    const long long i = (long long)blockIdx.x * SPLIT_NT + threadIdx.x;
+    double a = 0.0, b = 0.0;
+    if (i < n) {
+        const float2 zv = z[i];
+        const double2 rv = r[i], pv = rp[i];
+        a = fma((double)zv.x, rv.x, (double)zv.y * rv.y);
+        b = fma((double)zv.x, pv.x, (double)zv.y * pv.y);
+    }
+    const double rr = fs_rr(part_rr, pending ? ntiles : 0, lds);
+    if (lead) {  // the sums below are not looked at when this ends the solve
+        *s1 = *s0;
+        s1->pending = 0;
+        if (pending) f_finalize(s1, FF_UPD, rr, 0.0);
+    }
+    a = split_total(a, lda);
+    b = split_total(b, ldb);
+    if (threadIdx.x == 0) {
+        part_z[2 * blockIdx.x] = a;
+        part_z[2 * blockIdx.x + 1] = b;
+    }
+}
+
+// p = z + beta p, beta from the partials of k_fs_z
+__global__ __launch_bounds__(SPLIT_NT) void k_fs_p(double2 *__restrict__ p, const float2 *__restrict__ z, long long n,
+                                                   const double *__restrict__ part_z, int nz,
+                                                   const FState *__restrict__ s1, FState *__restrict__ s2)
+{
+    __shared__ double lda[SPLIT], ldb[SPLIT];
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    if (s1->flags.done) {
+        if (lead) *s2 = *s1;
+        return;
+    }
+    const bool first = s1->iter == 0;
+    const double zr_old = s1->zr_old;
+    const long long i = (long long)blockIdx.x * SPLIT_NT + threadIdx.x;
+    double2 pv = make_double2(0.0, 0.0);
+    float2 zv = make_float2(0.0f, 0.0f);
+    if (i < n) {
+        zv = z[i];
+        if (!first) pv = p[i];  // not written before the first direction
+    }
+    double zz[2] = { 0.0, 0.0 };
+    strided_sums<SPLIT_NT, 2, 2>(part_z, nz, zz);
+    const double a = split_total(zz[0], lda), b = split_total(zz[1], ldb);
+    if (lead) {
+        *s2 = *s1;
+        f_finalize(s2, FF_Z, a, b);
+    }
+    if (!(a > 0.0) || !isfinite(a) || i >= n) return;  // as FF_Z decides
+    const double beta = first ? 0.0 : (a - b) / zr_old;
+    p[i] = make_double2(fma(beta, pv.x, (double)zv.x), fma(beta, pv.y, (double)zv.y));
+}
+
+// t = D_oe p ; partials of <p, A p>
+template <bool KEEP>
+__global__ __launch_bounds__(SPLIT_NT) void k_fs_Dp(Geom g, const char *__restrict__ fat,
+                                                    const char *__restrict__ lng, const double *__restrict__ p,
+                                                    double *__restrict__ t, double *__restrict__ part_pap,
+                                                    const FState *__restrict__ s2)
+{
+    using T = SplitTerms<PF64, KEEP>;
+    __shared__ __align__(16) double red[SPLIT * TILE_REALS];
+    __shared__ double ldp[SPLIT];
+    if (s2->flags.done) return;
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    if (tile >= g.ntiles) return;
+    const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = tile * TILE + lane;
+    T terms;
+    terms.load(g, fat, lng, 1, tile, lane, h < g.Vh ? h : g.Vh - 1, q);
+    const double2 *pv = reinterpret_cast<const double2 *>(p);
+    double2 f[3], l[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        f[a] = pv[(size_t)terms.nf * 3 + a];
+        l[a] = pv[(size_t)terms.nl * 3 + a];
+    }
+    const int i = threadIdx.x;
+    const bool own = i < min(TILE_REALS, (g.Vh - tile * TILE) * 6);
+    const size_t at = (size_t)tile * TILE_REALS + i;
+    const double po = own ? p[at] : 0.0;
+    double acc[6];
+    terms.products(f, l, acc);
+    T::put(acc, q, lane, red);
+    __syncthreads();
+    double s = 0.0;
+    if (own) {
+        const double tv = T::result(red, i);
+        t[at] = tv;
+        s = fma(s2->m4 * po, po, tv * tv);
+    }
+    split_partial(s, ldp, part_pap + tile);
+}
+
+// A p = m4 p - D_eo t in registers ; x += alpha p ; r_prev = r ; r -= alpha A p ;
+// r32 = float(r) ; partials of |r|^2.  alpha from the partials of k_fs_Dp.
+template <bool KEEP>
+__global__ __launch_bounds__(SPLIT_NT) HISQ_WAVES(4) void k_fs_upd(
+    Geom g, const char *__restrict__ fat, const char *__restrict__ lng, const double2 *__restrict__ t,
+    const double *__restrict__ p, double *__restrict__ x, double *__restrict__ r, double *__restrict__ rp,
+    float *__restrict__ r32, const double *__restrict__ part_pap, double *__restrict__ part_rr,
+    const FState *__restrict__ s2, FState *__restrict__ s0)
+{
+    using T = SplitTerms<PF64, KEEP>;
+    __shared__ __align__(16) double red[SPLIT * TILE_REALS];
+    __shared__ double lds[SPLIT], ldp[SPLIT];
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    if (tile >= g.ntiles) return;
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;  // workgroup 0 has tile 0
+    if (s2->flags.done) {
+        if (lead) *s0 = *s2;
+        return;
+    }
+    const double zr = s2->zr, m4 = s2->m4;
+    double pap[1] = { 0.0 };
+    strided_sums<SPLIT_NT, 1, 2>(part_pap, g.ntiles, pap);
+    const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = tile * TILE + lane;
+    T terms;
+    terms.load(g, fat, lng, 0, tile, lane, h < g.Vh ? h : g.Vh - 1, q);
+    double2 f[3], l[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        f[a] = t[(size_t)terms.nf * 3 + a];
+        l[a] = t[(size_t)terms.nl * 3 + a];
+    }
+    const int i = threadIdx.x;
+    const bool own = i < min(TILE_REALS, (g.Vh - tile * TILE) * 6);
+    const size_t at = (size_t)tile * TILE_REALS + i;
+    double po = 0.0, xo = 0.0, ro = 0.0;
+    if (own) {
+        po = p[at];
+        xo = x[at];
+        ro = r[at];
+    }
+    double acc[6];
+    terms.products(f, l, acc);
+    T::put(acc, q, lane, red);
+    const double total = split_total(pap[0], lds);  // its barrier also publishes `red`
+    if (lead) {
+        *s0 = *s2;
+        f_finalize(s0, FF_PAP, total, 0.0);
+        s0->pending = s0->flags.done ? 0 : 1;
+    }
+    if (!(total > 0.0) || !isfinite(total)) return;  // as FF_PAP decides
+    double s = 0.0;
+    if (own) {
+        const double a = zr / total, app = fma(m4, po, -T::result(red, i));
+        rp[at] = ro;
+        xo = fma(a, po, xo);
+        ro = fma(-a, app, ro);
+        x[at] = xo;
+        r[at] = ro;
+        r32[at] = (float)ro;  // the next application's network input
+        s = ro * ro;
+    }
+    split_partial(s, ldp, part_rr + tile);
+}
+
+// The last iteration's |r|^2 into the state, before the host reads it.
+__global__ __launch_bounds__(SPLIT_NT) void k_fs_settle(const double *__restrict__ part_rr, int n, FState *s0)
+{
+    __shared__ double lds[SPLIT];
+    if (s0->flags.done || !s0->pending) return;
+    const double v = fs_rr(part_rr, n, lds);
+    if (threadIdx.x == 0) {
+        s0->pending = 0;
+        f_finalize(s0, FF_UPD, v, 0.0);
+    }
+}
+
 __global__ void k_f_init(FState *st, double tol2, double m4)
 {
     if (threadIdx.x || blockIdx.x) return;
     st->flags.done = 0;
     st->flags.reliable = 0;
-    st->iter = st->fallback = st->window_start = 0;
+    st->iter = st->fallback = st->window_start = st->pending = 0;
     st->rr_window = 0.0;
     st->m4 = m4;
     st->stop2 = tol2;
@@ -358,9 +573,37 @@ static int fcg_impl(double mass, double tol, const void *fat, const void *lng, c
         stats.time_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         return HISQ_OK;
     }
+    // The four-kernel form: its states and partials lie in the slot of z, which it does not store.
+    const int nz = (int)((n + SPLIT_NT - 1) / SPLIT_NT);
+    const size_t head = (sizeof(FState) + 63) & ~(size_t)63;
+    const bool split = split_tiles(g, HISQ_F64) &&
+                       2 * head + (2 * (size_t)g.ntiles + 2 * (size_t)nz) * sizeof(double) <= v64;
+    const bool keep = links_stay_cached(g, HISQ_F64);
+    FState *s1 = (FState *)z, *s2 = (FState *)((char *)z + head);
+    double *part_pap = (double *)((char *)z + 2 * head), *part_rr = part_pap + g.ntiles, *part_z = part_rr + g.ntiles;
+    auto split_iter = [&](hipStream_t q) -> hipError_t {
+        const dim3 gv(nz), gt(xcd_grid(g.ntiles)), nt(SPLIT_NT);
+        hipLaunchKernelGGL(k_fs_z, gv, nt, 0, q, z32, (const double2 *)r, (const double2 *)rp, n,
+                           (const double *)part_rr, g.ntiles, part_z, (const FState *)st, s1);
+        hipLaunchKernelGGL(k_fs_p, gv, nt, 0, q, pv, z32, n, (const double *)part_z, nz, (const FState *)s1, s2);
+        auto dp = keep ? k_fs_Dp<true> : k_fs_Dp<false>;
+        hipLaunchKernelGGL(dp, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double *)pv, (double *)t,
+                           part_pap, (const FState *)s2);
+        auto upd = keep ? k_fs_upd<true> : k_fs_upd<false>;
+        hipLaunchKernelGGL(upd, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double2 *)t,
+                           (const double *)pv, (double *)x, (double *)r, (double *)rp, (float *)r32,
+                           (const double *)part_pap, part_rr, (const FState *)s2, st);
+        return hipGetLastError();
+    };
+    auto settle = [&](hipStream_t q) -> hipError_t {
+        if (!split) return hipSuccess;
+        hipLaunchKernelGGL(k_fs_settle, dim3(1), dim3(SPLIT_NT), 0, q, (const double *)part_rr, g.ntiles, st);
+        return hipGetLastError();
+    };
     auto iter = [&](hipStream_t q) -> hipError_t {
         int rc = net_layers_dispatch(g, fat32, W, C, acts, 1, q);
         if (rc) return hipErrorUnknown;
+        if (split) return split_iter(q);
         hipLaunchKernelGGL(k_f_z, gb, dim3(F_NT), 0, q, z32, z, (const double2 *)r, (const double2 *)rp,
                            n, part, (const FState *)st);
         hipLaunchKernelGGL(k_f_fin, dim3(1), dim3(256), 0, q, (const double *)part, nbf, 1, st, (int)FF_Z);
@@ -387,6 +630,7 @@ static int fcg_impl(double mass, double tol, const void *fat, const void *lng, c
             HISQ_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
             hipError_t e = hipSuccess;
             for (int k = 0; k < K && e == hipSuccess; ++k) e = iter(cs);
+            if (e == hipSuccess) e = settle(cs);
             hipGraph_t gtmp = nullptr;
             hipError_t e2 = hipStreamEndCapture(cs, &gtmp);
             if (e != hipSuccess || e2 != hipSuccess) {
@@ -401,7 +645,7 @@ static int fcg_impl(double mass, double tol, const void *fat, const void *lng, c
             const int k = std::min(K, o.max_iter - queued);
             hipError_t e = hipSuccess;
             if (exec && k == K) e = hipGraphLaunch(exec, s);
-            else for (int i = 0; i < k && e == hipSuccess; ++i) e = iter(s);
+            else for (int i = 0; i <= k && e == hipSuccess; ++i) e = i < k ? iter(s) : settle(s);
             if (e == hipSuccess) e = hipMemcpyAsync(hs, st, sizeof(FState), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             if (e != hipSuccess) { rc = hip_fail(e, "fcg_solve: iteration"); break; }

@@ -549,6 +549,36 @@ def _fcg(hq, dims, mass, fat, lng, b, w, C, max_iter=0):
     return xd.cpu().numpy(), st
 
 
+# four kernels of its own per iteration up to 768 tiles, eight beyond; 6x4x4x10 and 6^4 have ragged tiles.  The
+# workspace starts as NaN: nothing is read before it is written.
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 4, 10), (6, 6, 6, 6), (16, 16, 16, 24), (18, 16, 16, 24)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_fcg_kernel_forms(hq, dims):
+    import torch
+    from paper_1411_2087_amd import train
+    mass, C = 0.3, 4
+    fat, lng = fields(dims, synth.gauge_seed(3))
+    b = synth.source(dims, synth.source_seed(3))
+    L64 = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F64)
+    L32 = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F32)
+    bd = torch.from_numpy(b).cuda()
+    wd = torch.from_numpy(train.flatten(train.identity_weights(C)).astype(np.complex64)).cuda()
+    ws = hq.fields.workspace("fcg", dims, 1, 0, C)
+    got = []
+    for check, graph in ((0, 1), (0, 0), (7, 1)):
+        ws.fill_(0xFF)
+        xd = torch.zeros_like(bd)
+        opts = hq.CGOpts(mode=0, max_iter=0, check_every=check, use_graph=graph, delta=0.1)
+        st = hq.fcg_solve(mass, CG_TOL, L64.fat, L64.lng, L32.fat, wd, C, bd, xd, dims, opts, ws)
+        assert st["rc"] == 0 and st["fallback_used"] == 0
+        got.append((st["iters"], xd.cpu().numpy()))
+    tr = oracle.true_residual(dims, mass, fat, lng, b, got[0][1])
+    say(f"fcg forms {dims}: iters={[i for i, _ in got]} oracle resid={tr:.2e}")
+    assert tr <= CG_TOL
+    for it, y in got[1:]:
+        assert it == got[0][0] and np.array_equal(y, got[0][1])
+
+
 def test_fcg_identity_is_cg(hq):
     from paper_1411_2087_amd import train
     dims, mass, C = (8, 8, 8, 8), 0.05, 4
