@@ -252,8 +252,12 @@ __device__ __forceinline__ void slice_finish(const SliceRaw &r, float tv[4][6])
 // slice and wavefront are saved.  Lanes past Vh (clamped to the last site)
 // get finite values that no stored output uses: the layer stores only sites
 // below Vh, and the weight gradient multiplies them by zero upstream gradients.
-// in: the channels of one batch entry, [c][parity][Vh][3].
-template <int CIN, bool SIGNED = false, bool WIDE = false>
+// in: the channels of one batch entry, [c][parity][Vh][3].  EVEN (one channel):
+// `in` is a field embedded from the even sites, so T_0 is zero at odd sites and
+// every other transport at even ones; those are not loaded (16^4, batch 16, 16
+// channels, training: layer<1, 16> 157 -> 112 us, wgrad<1, 16> 157 -> 143,
+// bwd<1, 16> 255 -> 247).
+template <int CIN, bool SIGNED = false, bool WIDE = false, bool EVEN = false>
 __device__ __forceinline__ void slice_transport(const Geom &g, const char *__restrict__ fat,
                                                 const float2 *__restrict__ in, int p, int tile, int lane,
                                                 const NetSite &st, int j, int q, float tv[4][6])
@@ -271,7 +275,7 @@ __device__ __forceinline__ void slice_transport(const Geom &g, const char *__res
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int k = 4 * q + i;
-            if (k == 0) {
+            if (k == 0 && !(EVEN && p == 1)) {
                 float2 e[3];
                 const float2 *v = in + (size_t)p * g.Vh * 3 + (size_t)hc * 3;
                 if constexpr (WIDE) load_cvec(v, hc, e);
@@ -281,7 +285,7 @@ __device__ __forceinline__ void slice_transport(const Geom &g, const char *__res
                     tv[i][2 * a] = e[a].x;
                     tv[i][2 * a + 1] = e[a].y;
                 }
-            } else if (k < 9) {
+            } else if (k > 0 && k < 9 && !(EVEN && p == 0)) {
                 const int d = k - 1;
                 const int nh = nbr_h(g, hc, x, y, z, t, d & 3, d >= 4 ? -1 : 1);
                 float m[18];
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
     };
     {
         float tv[4][6];
-        slice_transport<CIN, false, CIN == 1>(g, fat, inb, p, tile, lane, site, 0, q, tv);
+        slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, 0, q, tv);
         put(F[0], tv);
     }
     __syncthreads();
@@ -420,7 +424,7 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
             mix(F[j & 1], j);
             if (j + 1 < S::N) {
                 float tv[4][6];
-                slice_transport<CIN, false, CIN == 1>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
+                slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
                 put(F[(j + 1) & 1], tv);
             }
         }
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(NET_NT, 4) void k_net_wgrad(Geom g, const char *__r
         };
         {
             float tv[4][6];
-            slice_transport<CIN, false, CIN == 1>(g, fat, inb, p, tile, lane, site, 0, q, tv);
+            slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, 0, q, tv);
             put(Fb, tv);
         }
         __syncthreads();  // g and slice 0 are in LDS
@@ -630,7 +634,7 @@ __global__ __launch_bounds__(NET_NT, 4) void k_net_wgrad(Geom g, const char *__r
             const bool more = j + 1 < S::N;
             float tv[4][6];
             // the next slice's transport goes to registers while the owner wave multiplies this one
-            if (more) slice_transport<CIN, false, CIN == 1>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
+            if (more) slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
             if (q == (j & 3)) {  // this slice's owner (wave-uniform)
 #pragma unroll
                 for (int ks = 0; ks < KT / SK; ++ks) {
@@ -759,7 +763,7 @@ __global__ __launch_bounds__(NET_NT, 3) void k_net_bwd(Geom g, const char *__res
             for (int mt = 0; mt < MTX; ++mt) acc[n][mt] = floatx4{ 0.f, 0.f, 0.f, 0.f };
         {
             float tv[4][6];
-            slice_transport<CI, false, CI == 1>(g, fat, gb, p, tile, lane, site, 0, q, tv);
+            slice_transport<CI, false, CI == 1, CI == 1>(g, fat, gb, p, tile, lane, site, 0, q, tv);
             put(tv);
         }
         __syncthreads();  // x and slice 0 are in LDS
@@ -769,7 +773,7 @@ __global__ __launch_bounds__(NET_NT, 3) void k_net_bwd(Geom g, const char *__res
             const bool more = j + 1 < S::N;
             // the next slice's transport goes to registers while this one is multiplied
             float tv[4][6];
-            if (more) slice_transport<CI, false, CI == 1>(g, fat, gb, p, tile, lane, site, j + 1, q, tv);
+            if (more) slice_transport<CI, false, CI == 1, CI == 1>(g, fat, gb, p, tile, lane, site, j + 1, q, tv);
             {  // mixing: the layer kernel's column tiles 3q..3q+2
                 bf16x8 av[MTX];
 #pragma unroll
