@@ -506,7 +506,9 @@ static_assert(sizeof(FState) <= PIN_SLOT_BYTES, "FState does not fit its pinned 
 // channel); the embedding and extraction of the even vector.  Per even site:
 // two FP64 Dslash link streams and 20 FP64-vector equivalents of streams
 // (r to FP32, z from FP32 with the two dot products, p, the two Dslash
-// sources and outputs, A p, x, r, r_prev).
+// sources and outputs, A p, x, r, r_prev).  It is the count of the eight-kernel
+// form with the whole last layer; the four-kernel form does not store z and
+// A p, and the last layer leaves out the odd sites, so both move less than this.
 static double fcg_iter_bytes(const Geom &g, int C)
 {
     const double layers = 4 * 4 * 72.0 + 24.0 * ((1 + C) + 2 * (C + C) + (C + 1));
