@@ -160,6 +160,10 @@ __global__ __launch_bounds__(PACK_NT) void k_pack(Lex l, Geom g, const double2 *
                                                   char *__restrict__ out, int hop, size_t block_bytes, int *status)
 {
     __shared__ Stage<PACK_NT> st;
+    // without ROWS: a status word to clear for the kernel that follows (a fill launch of its own costs more than
+    // this kernel on the smallest lattices)
+    if constexpr (std::is_void<ROWS>::value)
+        if (status && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *status = 0;
     const int blk = xcd_block(blockIdx.x, gridDim.x);
     const long long n = (long long)blk * PACK_NT + threadIdx.x;
     if ((long long)blk * PACK_NT >= l.V) return;
@@ -265,16 +269,14 @@ extern "C" int hisq_pack_links(const void *fat_canon, const void *long_canon, co
     // where the sites alone do not fill the chip (4 workgroups per CU), the directions are shared out too
     const int nb = (int)((l.V + PACK_NT - 1) / PACK_NT), split = nb >= 1024 ? 1 : nb >= 256 ? 4 : 8;
     const dim3 grid(xcd_grid(nb), split), block(PACK_NT);
-    auto full = [&](auto kernel, const void *in, void *out, int hop, size_t bytes) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, l, g, (const double2 *)in, (char *)out, hop, bytes,
-                           (int *)nullptr);
+    auto full = [&](auto kernel, const void *in, void *out, int hop, size_t bytes, int *clear = nullptr) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, l, g, (const double2 *)in, (char *)out, hop, bytes, clear);
     };
     if (prec == HISQ_F64C || prec == HISQ_F32C || prec == HISQ_I16SC) {
         const int fp = prec == HISQ_F64C ? HISQ_F64 : (prec == HISQ_F32C ? HISQ_F32 : HISQ_I16S);
-        full(fp == HISQ_F64 ? k_pack<HISQ_F64, void> : fp == HISQ_F32 ? k_pack<HISQ_F32, void> : k_pack<HISQ_I16S, void>,
-             fat_canon, fat_out, 1, dir_block_bytes(fp));
         int *status = reinterpret_cast<int *>((char *)long_out + long_field_bytes(g, prec) - 256);
-        HISQ_HIP(hipMemsetAsync(status, 0, sizeof(int), s));
+        full(fp == HISQ_F64 ? k_pack<HISQ_F64, void> : fp == HISQ_F32 ? k_pack<HISQ_F32, void> : k_pack<HISQ_I16S, void>,
+             fat_canon, fat_out, 1, dir_block_bytes(fp), status);
         hipLaunchKernelGGL((prec == HISQ_F64C   ? k_pack<HISQ_F64C, PF64R>
                             : prec == HISQ_F32C ? k_pack<HISQ_F32C, PF32R>
                                                 : k_pack<HISQ_I16SC, PI16R>),
