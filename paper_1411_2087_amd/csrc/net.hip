@@ -255,8 +255,8 @@ __device__ __forceinline__ void slice_finish(const SliceRaw &r, float tv[4][6])
 // in: the channels of one batch entry, [c][parity][Vh][3].  EVEN (one channel):
 // `in` is a field embedded from the even sites, so T_0 is zero at odd sites and
 // every other transport at even ones; those are not loaded (16^4, batch 16, 16
-// channels, training: layer<1, 16> 157 -> 112 us, wgrad<1, 16> 157 -> 143,
-// bwd<1, 16> 255 -> 247).
+// channels: wgrad<1, 16> 157 -> 143 us, bwd<1, 16> 255 -> 247; batch 1, 4
+// channels: layer<1, 4> 9.6 -> 7.6).
 template <int CIN, bool SIGNED = false, bool WIDE = false, bool EVEN = false>
 __device__ __forceinline__ void slice_transport(const Geom &g, const char *__restrict__ fat,
                                                 const float2 *__restrict__ in, int p, int tile, int lane,
@@ -363,6 +363,11 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
     using S = Slices<CIN>;
     constexpr int MT = (2 * COUT + 15) / 16;  // 16-row tiles of the output
     constexpr int PB = SK + 8;                // LDS pitch of a column (bf16)
+    // The zero half of an embedded input is not loaded, but for 16 channels: there, calls that alternate between
+    // states beyond the last-level cache were slower for it where the activations are about its size (12x14x12x8,
+    // batch 8: 179 us with the loads, 182 without; 16^4, batch 4: 338, 341), although this kernel is faster and
+    // most other sizes gain 1-2 %.  Fewer channels gain 0-5 % and lose nowhere (12^4, 4 channels, batch 16: 180, 171).
+    constexpr bool SKIP = CIN == 1 && COUT < 16;
     __shared__ __align__(16) __bf16 F[2][NCOL * PB];  // two slices: one mixed while the next is written
     const int u = xcd_block(blockIdx.x, gridDim.x);
     if (u >= batch * 2 * g.ntiles) return;  // the grid is rounded up to a multiple of the XCD count
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
     };
     {
         float tv[4][6];
-        slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, 0, q, tv);
+        slice_transport<CIN, false, CIN == 1, SKIP>(g, fat, inb, p, tile, lane, site, 0, q, tv);
         put(F[0], tv);
     }
     __syncthreads();
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
             mix(F[j & 1], j);
             if (j + 1 < S::N) {
                 float tv[4][6];
-                slice_transport<CIN, false, CIN == 1, CIN == 1>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
+                slice_transport<CIN, false, CIN == 1, SKIP>(g, fat, inb, p, tile, lane, site, j + 1, q, tv);
                 put(F[(j + 1) & 1], tv);
             }
         }
