@@ -366,7 +366,8 @@ __global__ __launch_bounds__(NET_NT) void k_net_layer(Geom g, const char *__rest
     // The zero half of an embedded input is not loaded, but for 16 channels: there, calls that alternate between
     // states beyond the last-level cache were slower for it where the activations are about its size (12x14x12x8,
     // batch 8: 179 us with the loads, 182 without; 16^4, batch 4: 338, 341), although this kernel is faster and
-    // most other sizes gain 1-2 %.  Fewer channels gain 0-5 % and lose nowhere (12^4, 4 channels, batch 16: 180, 171).
+    // most other sizes gain 1-2 %.  With fewer channels, five shapes measured gain 0-5 % (12^4, 4 channels, batch 16:
+    // 180, 171).
     constexpr bool SKIP = CIN == 1 && COUT < 16;
     __shared__ __align__(16) __bf16 F[2][NCOL * PB];  // two slices: one mixed while the next is written
     const int u = xcd_block(blockIdx.x, gridDim.x);
