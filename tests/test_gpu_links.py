@@ -192,3 +192,23 @@ def test_pack_places_every_matrix(hq, dims):
     neg = np.linalg.det(m).real < 0
     word = (neg.astype(np.uint64) << np.arange(64, dtype=np.uint64)).sum(-1, dtype=np.uint64)
     assert np.array_equal(sign, word)
+
+
+@pytest.mark.parametrize("coeff", [FAT7[:4] + (-1 / 16,), FAT7, (0, 1.0, 0, 0, 0), (0, 0, 1.0, 0, 0), (0, 0, 0, 1.0, 0),
+                                   (0, 0, 0, 0, 1.0)], ids=["lepage7", "fat7", "staple3", "staple5", "staple7", "lepage"])
+def test_fat_paths_round_no_more_than_the_staples(hq, coeff):
+    """The error of the three passes against extended precision is not above that of the same sum taken staple by
+    staple (the schedule of the small workspace).  Both round every product at its own size and add it once; the
+    ratio of two root-mean-square errors over 93 312 reals each scatters by about 0.3 %, so 2 % is its bound."""
+    import torch
+    dims = (6, 6, 6, 6)
+    U = synth.thin_links(dims, synth.gauge_seed(8))
+    ref = K.fat_paths(dims, U.astype(np.clongdouble), coeff)
+    field = (U.shape[1] * 144 + 255) // 256 * 256
+    rms = []
+    for ws in (hq.fields.workspace("fat_paths", dims), torch.empty(3 * field, dtype=torch.uint8, device="cuda")):
+        out = torch.full((4, U.shape[1], 3, 3), float("nan"), dtype=torch.complex128, device="cuda")
+        hq.hisq_fat_paths(dev(U), coeff, out, dims, ws)
+        rms.append(float(np.sqrt(np.mean(np.abs(out.cpu().numpy() - ref) ** 2))))
+    say(f"fat paths {coeff}: rms error {rms[0]:.3e}, staple by staple {rms[1]:.3e}")
+    assert rms[0] <= 1.02 * rms[1]
