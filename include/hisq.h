@@ -406,10 +406,12 @@ int hisq_three_link(const void *thin, void *out, const int dims[4], void *stream
  * 7-staples (one more distinct axis: 48) and Lepage paths (a 3-staple
  * around a 3-staple in the same nu with the same sign: 6).  The weights are
  * inputs: the paper does not fix them.  workspace: device memory of
- * hisq_workspace_bytes("fat_paths", dims, 0, 0, 0) bytes (ten one-direction
- * link fields); with less, but at least three fields (each a multiple of 256
- * bytes), the same sums are taken path family by path family, at a third of
- * the speed.  out must not overlap thin or the workspace. */
+ * hisq_workspace_bytes("fat_paths", dims, 0, 0, 0) bytes: ten one-direction
+ * link fields (each rounded up to whole 64-site tiles), or three (each rounded
+ * up to 256 bytes) where ten are more than 64 GiB.  Any size from three fields
+ * on is accepted; with fewer than ten the same sums are taken path family by
+ * path family, at a third of the speed.  out must not overlap thin or the
+ * workspace. */
 int hisq_fat_paths(const void *thin, const double coeff[5], void *out, const int dims[4], void *workspace,
                    size_t ws_bytes, void *stream);
 

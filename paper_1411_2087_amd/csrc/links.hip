@@ -549,12 +549,17 @@ static int check_launch(const char *what)
 // gets the staple-by-staple schedule.
 static size_t tiled_field_bytes(const Lex &l) { return (size_t)((l.V + TILE - 1) / TILE) * TILE * 144; }
 static size_t fat_paths_min_bytes(const Lex &l) { return 3 * align_up((size_t)l.V * 144, 256); }
+static size_t fat_paths_pass_bytes(const Lex &l) { return 10 * tiled_field_bytes(l); }
 
+// What the workspace query asks for: beyond 64 GiB (48 million sites) three
+// fields, not ten.  thin and out take eight more, so that with ten a 96^3 x 192
+// lattice needs 440 GB; with three it fits the card (269 of 288 GB).
 size_t fat_paths_ws_bytes(const int dims[4])
 {
     Lex l;
     if (make_lex(dims, l)) return 0;
-    return 10 * tiled_field_bytes(l);
+    const size_t full = fat_paths_pass_bytes(l);
+    return full <= (size_t)64 << 30 ? full : fat_paths_min_bytes(l);
 }
 
 }  // namespace hisq
@@ -590,8 +595,8 @@ extern "C" int hisq_fat_paths(const void *thin, const double coeff[5], void *out
         if (!std::isfinite(coeff[i])) return fail(HISQ_EINVAL, "hisq_fat_paths: coefficient not finite");
     const size_t bytes = (size_t)l.V * 4 * 144;
     if (overlaps(thin, bytes, out, bytes)) return fail(HISQ_EALIAS, "hisq_fat_paths: out overlaps thin");
-    const bool passes = ws_bytes >= fat_paths_ws_bytes(dims) && l.V < (1LL << 31);  // sites are ints there
-    const size_t need = passes ? fat_paths_ws_bytes(dims) : fat_paths_min_bytes(l);
+    const bool passes = ws_bytes >= fat_paths_pass_bytes(l) && l.V < (1LL << 31);  // sites are ints there
+    const size_t need = passes ? fat_paths_pass_bytes(l) : fat_paths_min_bytes(l);
     if (!workspace || ws_bytes < need)
         return fail(HISQ_EWORKSPACE, "hisq_fat_paths: workspace NULL or smaller than hisq_workspace_bytes()");
     if (overlaps(workspace, need, thin, bytes) || overlaps(workspace, need, out, bytes))

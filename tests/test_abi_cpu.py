@@ -190,3 +190,16 @@ def test_alignment_validation_without_gpu():
         assert call() == -1, name
         assert b"16-byte aligned" in lib.hisq_last_error(), (name, lib.hisq_last_error())
 
+
+
+@pytest.mark.parametrize("dims,fields", [((4, 4, 4, 4), 10), ((32, 32, 32, 32), 10), ((48, 48, 48, 96), 10),
+                                         ((64, 64, 64, 180), 10), ((64, 64, 64, 184), 3), ((96, 96, 96, 128), 3),
+                                         ((96, 96, 96, 192), 3)], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_fat_paths_workspace_leaves_room_for_the_links(dims, fields):
+    """Every lattice whose thin and smeared links and three workspace fields fit 288 GB still fits with the workspace
+    that the query asks for; up to 64 GiB the query asks for the ten fields of the fast schedule."""
+    import paper_1411_2087_amd as hq
+    field = int(np.prod(dims)) * 144
+    ws = hq.hisq_workspace_bytes("fat_paths", dims, 0, 0, 0)
+    assert fields * field <= ws <= fields * (field + 64 * 144)
+    assert 11 * field > 288e9 or 8 * field + ws <= 288e9
