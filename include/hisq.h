@@ -236,23 +236,34 @@ int hisq_dot_noalloc(const void *x, const void *y, long long n, int prec, double
  * buffers (dst = D src on parity 1, `reps` launches each, 20 if <= 0),
  * remembers the fastest for (dims, prec) in this process -- and in the file
  * named by the environment variable HISQ_TUNE_CACHE, if set -- and uses it
- * in every later Dslash of that lattice and precision (lattices of few
- * 64-site tiles per parity -- at most 768 in HISQ_F64, 1280 in HISQ_F64C,
- * HISQ_F32 and HISQ_F32C, 2600 with 16-bit links -- take one form of their
- * own, whatever the shape).  The plain CG's fused
- * kernels take the tile order of the chosen shape; for HISQ_F64 a shape with
- * a blocked tile order is chosen only when it is more than 3 % faster than
- * the fastest plain-order shape (the blocked orders slow the CG solve down
- * although the bare Dslash times them close to the plain one).  All shapes give
- * bitwise-identical results.  best_shape (may be NULL) receives the chosen
- * index, us_per_shape (may be NULL, room for hisq_dslash_shape(dims, prec,
- * -2) entries) the measured microseconds.  Synchronises `stream`. */
+ * in every later Dslash of that lattice and precision.
+ *
+ * Lattices of few 64-site tiles per parity -- at most 768 in HISQ_F64, 1280
+ * in HISQ_F64C, HISQ_F32 and HISQ_F32C, 2600 with 16-bit links -- have a form
+ * beside the shapes, a workgroup per tile, and run it unless
+ * hisq_dslash_shape has set a shape.  There this call times that form too;
+ * the shape is used only if it is faster, and a shape set before no longer
+ * counts.
+ *
+ * The plain CG's fused kernels take the tile order of the chosen shape; for
+ * HISQ_F64 a shape with a blocked tile order is chosen only when it is more
+ * than 3 % faster than the fastest plain-order shape (the blocked orders slow
+ * the CG solve down although the bare Dslash times them close to the plain
+ * one).  All shapes give bitwise-identical results; the form of the small
+ * lattices adds the same terms in another order.  best_shape (may be NULL)
+ * receives the index of the fastest shape, us_per_shape (may be NULL, room
+ * for hisq_dslash_shape(dims, prec, -2) entries) the measured microseconds.
+ * Synchronises `stream`. */
 int hisq_tune_dslash(const void *fat, const void *lng, const void *src, void *dst, const int dims[4], int prec,
                      int reps, int *best_shape, double *us_per_shape, void *stream);
 
 /* Launch shape of the single-RHS Dslash for (dims, prec): shape >= 0 sets
- * it, shape == -1 only queries; returns the shape in use, or a negative
- * hisq_status.  shape == -2 returns the number of shapes. */
+ * it, on every lattice; shape == -1 only queries; returns the shape chosen
+ * (set, tuned or the default), or a negative hisq_status.  shape == -2
+ * returns the number of shapes.  On the small lattices that have a form of
+ * their own (hisq_tune_dslash) setting a shape, also the one that the query
+ * returned, takes them out of it; hisq_tune_dslash puts them back where it is
+ * the faster one. */
 int hisq_dslash_shape(const int dims[4], int prec, int shape);
 
 /* Workspace bytes for `solver` = "cg", "cg_multi", "fcg", "fat_paths" or

@@ -164,18 +164,28 @@ bool split_tiles(const Geom &g, int prec)
 // FP32 24^4 (382 MB) 35.2, 37.8.
 bool links_stay_cached(const Geom &g, int prec) { return 2.0 * g.Vh * link_bytes_site(prec) <= 256e6; }
 
-// the split form where the lattice asks for it; false: not launched
 template <class P, bool XM>
-static bool launch_split(const Geom &g, const void *fat, const void *lng, const void *src, const void *x, void *dst,
+static void launch_split(const Geom &g, const void *fat, const void *lng, const void *src, const void *x, void *dst,
                          double m4, int parity, hipStream_t s, const SolverFlags *flags = nullptr,
                          int gate = GATE_ALWAYS)
 {
     using R = typename P::real;
-    if (!split_tiles(g, P::prec)) return false;
     auto k = links_stay_cached(g, P::prec) ? k_dslash_split<P, true, XM> : k_dslash_split<P, false, XM>;
     hipLaunchKernelGGL(k, dim3(xcd_grid(g.ntiles)), dim3(SPLIT_NT), 0, s, g, (const char *)fat, (const char *)lng,
                        (const typename P::cvec *)src, (const R *)x, (R *)dst, m4, parity, flags, gate);
-    return true;
+}
+
+static bool runs_split(const Geom &g, int prec)
+{
+    return split_tiles(g, prec) && dslash_form(g, prec) == DslashForm::rule;
+}
+
+template <class P>
+hipError_t launch_dslash_tiles(const Geom &g, const void *fat, const void *lng, const void *src, void *dst, int parity,
+                               hipStream_t s)
+{
+    launch_split<P, false>(g, fat, lng, src, nullptr, dst, 0.0, parity, s);
+    return hipGetLastError();
 }
 
 template <class P>
@@ -204,15 +214,20 @@ template <class P>
 hipError_t launch_dslash(const Geom &g, const void *fat, const void *lng, const void *src, void *dst, int parity,
                          hipStream_t s, const SolverFlags *flags, int gate)
 {
-    if (launch_split<P, false>(g, fat, lng, src, nullptr, dst, 0.0, parity, s, flags, gate)) return hipGetLastError();
+    if (runs_split(g, P::prec)) {
+        launch_split<P, false>(g, fat, lng, src, nullptr, dst, 0.0, parity, s, flags, gate);
+        return hipGetLastError();
+    }
     return launch_dslash_shape<P>(tuned_dslash_shape(g, P::prec), g, fat, lng, src, dst, parity, s, flags, gate);
 }
 
-#define HISQ_INST(P)                                                                                             \
-    template hipError_t launch_dslash<P>(const Geom &, const void *, const void *, const void *, void *, int,    \
-                                         hipStream_t, const SolverFlags *, int);                                 \
-    template hipError_t launch_dslash_shape<P>(int, const Geom &, const void *, const void *, const void *,      \
-                                               void *, int, hipStream_t, const SolverFlags *, int);
+#define HISQ_INST(P)                                                                                                \
+    template hipError_t launch_dslash<P>(const Geom &, const void *, const void *, const void *, void *, int,       \
+                                         hipStream_t, const SolverFlags *, int);                                    \
+    template hipError_t launch_dslash_shape<P>(int, const Geom &, const void *, const void *, const void *, void *, \
+                                               int, hipStream_t, const SolverFlags *, int);                         \
+    template hipError_t launch_dslash_tiles<P>(const Geom &, const void *, const void *, const void *, void *, int, \
+                                               hipStream_t);
 HISQ_INST(PF64)
 HISQ_INST(PF32)
 HISQ_INST(PF16S)
@@ -230,7 +245,10 @@ static hipError_t launch_apply_A(const Geom &g, double mass, const void *fat, co
 {
     hipError_t e = launch_dslash<P>(g, fat, lng, x, tmp, 1, s);
     if (e != hipSuccess) return e;
-    if (launch_split<P, true>(g, fat, lng, tmp, x, y, 4.0 * mass * mass, 0, s)) return hipGetLastError();
+    if (runs_split(g, P::prec)) {
+        launch_split<P, true>(g, fat, lng, tmp, x, y, 4.0 * mass * mass, 0, s);
+        return hipGetLastError();
+    }
     const int nb = blocks_for(g, AXMY_NT);
     hipLaunchKernelGGL((k_dslash_axmy<P, AXMY_NT>), dim3(xcd_grid(nb)), dim3(AXMY_NT), 0, s, g,
                        (const char *)fat, (const char *)lng, (const typename P::cvec *)tmp,

@@ -202,8 +202,8 @@ inline double link_bytes_site(int prec)
 }
 inline double vec_bytes(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 48.0 : 24.0; }
 
-// Whether a lattice takes the split form in this precision, whatever launch
-// shape is chosen for it, and whether its packed links stay in the last-level
+// Whether a lattice takes the split form in this precision where no shape was
+// asked for (dslash_form), and whether its packed links stay in the last-level
 // cache from one launch to the next (dslash.hip).
 bool split_tiles(const Geom &g, int prec);
 bool links_stay_cached(const Geom &g, int prec);
@@ -222,8 +222,9 @@ __device__ __forceinline__ bool gate_closed(const SolverFlags *f, int gate)
     return gate == GATE_RELIABLE && !f->reliable;
 }
 
-// Launch helpers (defined in dslash.hip).  launch_dslash uses the shape the
-// autotuner chose for (dims, precision), launch_dslash_shape a given one.
+// Launch helpers (defined in dslash.hip).  launch_dslash uses the form and the
+// shape chosen for (dims, precision), launch_dslash_shape a given shape,
+// launch_dslash_tiles the split form.
 struct DslashShape {
     int nt;      // threads per block
     int waves;   // minimum wavefronts per SIMD the compiler must allow
@@ -235,7 +236,13 @@ extern const DslashShape DSLASH_SHAPES[N_DSLASH_SHAPES];
 int tuned_dslash_shape(const Geom &g, int prec);            // tune.cpp
 int tuned_choice(const char *kind, const Geom &g, int prec, int n, int fallback);
 void set_tuned_choice(const char *kind, const Geom &g, int prec, int n, int v);
-void set_tuned_dslash_shape(const Geom &g, int prec, int shape);
+
+// What a lattice that split_tiles() covers runs in this precision: the split
+// form (rule), or the shape, because a caller asked for it (set) or because
+// the autotuner timed it faster (tuned).  The other lattices run the shape.
+enum class DslashForm { rule = 0, set = 1, tuned = 2 };
+DslashForm dslash_form(const Geom &g, int prec);
+void set_dslash_choice(const Geom &g, int prec, int shape, DslashForm form);
 
 template <class P>
 hipError_t launch_dslash(const Geom &g, const void *fat, const void *lng, const void *src, void *dst, int parity,
@@ -243,5 +250,8 @@ hipError_t launch_dslash(const Geom &g, const void *fat, const void *lng, const 
 template <class P>
 hipError_t launch_dslash_shape(int shape, const Geom &g, const void *fat, const void *lng, const void *src, void *dst,
                                int parity, hipStream_t s, const SolverFlags *flags = nullptr, int gate = GATE_ALWAYS);
+template <class P>
+hipError_t launch_dslash_tiles(const Geom &g, const void *fat, const void *lng, const void *src, void *dst, int parity,
+                               hipStream_t s);
 
 }  // namespace hisq

@@ -5,6 +5,7 @@
 // loaded from and saved to it (a flat JSON object of integers).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -19,6 +20,9 @@ namespace hisq {
 static std::mutex g_mu;
 static std::map<std::string, int> g_table;
 static bool g_loaded = false;
+// entries of kind "dslash_form", -1 until the file has been read: the small-lattice Dslash, a few microseconds in
+// all, looks for its own entry only where there is one
+static std::atomic<int> g_forms{ -1 };
 
 // Architecture of the current device (e.g. "gfx950"), part of every key, so
 // that a cache file written on one GPU model is not applied to another.
@@ -86,12 +90,48 @@ int tuned_choice(const char *kind, const Geom &g, int prec, int n, int fallback)
     return it == g_table.end() ? fallback : it->second;
 }
 
+static void store_locked(const std::string &key, int v)
+{
+    g_table[key] = v;
+    save_locked();
+}
+
 void set_tuned_choice(const char *kind, const Geom &g, int prec, int n, int v)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     load_locked();
-    g_table[key_of(kind, g, prec, n)] = v;
-    save_locked();
+    store_locked(key_of(kind, g, prec, n), v);
+}
+
+static void count_forms_locked()
+{
+    int n = 0;
+    for (auto &kv : g_table) n += kv.first.find(":dslash_form:") != std::string::npos;
+    g_forms.store(n);
+}
+
+DslashForm dslash_form(const Geom &g, int prec)
+{
+    if (g_forms.load() == 0) return DslashForm::rule;
+    std::lock_guard<std::mutex> lk(g_mu);
+    load_locked();
+    if (g_forms.load() < 0) count_forms_locked();
+    auto it = g_table.find(key_of("dslash_form", g, prec, 1));
+    if (it == g_table.end()) return DslashForm::rule;
+    return it->second == (int)DslashForm::set ? DslashForm::set
+           : it->second == (int)DslashForm::tuned ? DslashForm::tuned
+                                                  : DslashForm::rule;
+}
+
+void set_dslash_choice(const Geom &g, int prec, int shape, DslashForm form)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    load_locked();
+    const std::string key = key_of("dslash_form", g, prec, 1);
+    if (form == DslashForm::rule) g_table.erase(key);
+    else g_table[key] = (int)form;
+    store_locked(key_of("dslash", g, prec, 1), shape);
+    count_forms_locked();
 }
 
 // Untuned default per precision: two terms unrolled at 5 waves per SIMD for
@@ -113,8 +153,6 @@ int tuned_dslash_shape(const Geom &g, int prec)
     int v = tuned_choice("dslash", g, prec, 1, def);
     return (v >= 0 && v < N_DSLASH_SHAPES) ? v : def;
 }
-
-void set_tuned_dslash_shape(const Geom &g, int prec, int shape) { set_tuned_choice("dslash", g, prec, 1, shape); }
 
 // Times `launch()` with HIP events on stream s: 2 warm-up launches, then
 // `reps` launches; returns microseconds per launch or a negative value.
@@ -158,7 +196,13 @@ static int tune_dslash_impl(const Geom &g, const void *fat, const void *lng, con
     // A blocked shape is kept only when it beats the best plain-order shape by more than 3 %.
     if (P::prec == HISQ_F64 && plain_i >= 0 && DSLASH_SHAPES[best_i].order != 0 && best_us > 0.97 * plain_us)
         best_i = plain_i;
-    set_tuned_dslash_shape(g, P::prec, best_i);
+    DslashForm form = DslashForm::rule;
+    if (split_tiles(g, P::prec)) {
+        const double us = time_launches([&]() { return launch_dslash_tiles<P>(g, fat, lng, src, dst, 1, s); }, reps, s);
+        if (us < 0) return fail(HISQ_EHIP, "autotune: timing failed");
+        if (best_us < us) form = DslashForm::tuned;
+    }
+    set_dslash_choice(g, P::prec, best_i, form);
     if (best) *best = best_i;
     return HISQ_OK;
 }
@@ -199,6 +243,6 @@ extern "C" int hisq_dslash_shape(const int dims[4], int prec, int shape)
     if (prec < HISQ_F64 || prec > HISQ_I16SC) return fail(HISQ_EINVAL, "hisq_dslash_shape: unknown precision");
     if (shape == -2) return N_DSLASH_SHAPES;
     if (shape < -2 || shape >= N_DSLASH_SHAPES) return fail(HISQ_EINVAL, "hisq_dslash_shape: no such shape");
-    if (shape >= 0) set_tuned_dslash_shape(g, prec, shape);
+    if (shape >= 0) set_dslash_choice(g, prec, shape, DslashForm::set);
     return tuned_dslash_shape(g, prec);
 }

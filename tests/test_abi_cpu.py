@@ -203,3 +203,25 @@ def test_fat_paths_workspace_leaves_room_for_the_links(dims, fields):
     ws = hq.hisq_workspace_bytes("fat_paths", dims, 0, 0, 0)
     assert fields * field <= ws <= fields * (field + 64 * 144)
     assert 11 * field > 288e9 or 8 * field + ws <= 288e9
+
+
+def test_a_set_shape_is_saved_and_read_back(tmp_path):
+    """hisq_dslash_shape writes the shape, and that it was set, to HISQ_TUNE_CACHE; another process reads them, and a
+    file without the second entry too."""
+    import subprocess
+    import sys
+    path = tmp_path / "tune.json"
+    env = dict(os.environ, HISQ_TUNE_CACHE=str(path))
+
+    def run(code):
+        code = f"import sys; sys.path.insert(0, {ROOT!r}); import paper_1411_2087_amd as hq; " + code
+        return subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=300,
+                              check=True).stdout.split()
+
+    assert run("print(hq.hisq_dslash_shape((8, 8, 8, 8), 1, 7))") == ["7"]
+    lines = [ln for ln in path.read_text().splitlines() if "8x8x8x8" in ln]
+    assert len(lines) == 2 and any(":dslash_form:" in ln and ln.rstrip(",").endswith(" 1") for ln in lines)
+    assert run("print(hq.hisq_dslash_shape((8, 8, 8, 8), 1))") == ["7"]
+    path.write_text("{\n" + next(ln for ln in lines if ":dslash:" in ln).rstrip(",") + "\n}\n")
+    assert run("print(hq.hisq_dslash_shape((8, 8, 8, 8), 1), hq.hisq_dslash_shape((8, 8, 8, 10), 1, 4))") == ["7", "4"]
+    assert len([ln for ln in path.read_text().splitlines() if ":" in ln]) == 3

@@ -243,3 +243,56 @@ def test_dslash_and_A_at_the_split_line(hq, prec, tol, dims):
     nrm = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
     say(f"A {dims} prec={prec}: normwise {nrm:.3e}")
     assert nrm <= tol
+
+
+# lattices that no other test sets a shape for; 6x4x6x6 and 6x6x6x10 have a ragged last tile, 16x8x4x6 has blocked orders
+@pytest.mark.parametrize("dims", [(4, 4, 4, 6), (6, 4, 6, 6), (6, 6, 6, 10), (16, 8, 4, 6)],
+                         ids=lambda d: "x".join(map(str, d)))
+@pytest.mark.parametrize("prec,tol", [(0, TOL_F64), (1, TOL_F32), (2, TOL_F16S), (3, TOL_I16S), (4, TOL_F64),
+                                      (5, TOL_F32), (6, TOL_I16S)])
+def test_a_shape_that_is_set_runs_on_small_lattices(hq, dims, prec, tol):
+    """Small lattices have a form of their own, which adds the terms in another order; a shape that the caller sets
+    runs instead of it, in the Dslash and in A, and tuning chooses between the two."""
+    import torch
+    fat, lng = fields(dims, 1700 + prec)
+    L = hq.fields.Links.pack(fat, lng, dims, prec)
+    src = synth.source(dims, 3300)
+    if prec not in (0, 4):
+        src = src.astype(np.complex64).astype(np.complex128)
+    s = torch.from_numpy(src).to(hq.fields.VEC_DTYPE[prec]).cuda()
+
+    def both():
+        out = []
+        for parity in (0, 1):
+            d = torch.full_like(s, float("nan"))
+            hq.dslash_apply(L.fat, L.lng, s, d, parity, dims, prec)
+            out.append(d.cpu().numpy())
+        y = torch.full_like(s, float("nan"))
+        hq.hisq_apply_A(0.07, L.fat, L.lng, s, y, torch.empty_like(s), dims, prec)
+        return out + [y.cpu().numpy()]
+
+    own = both()
+    n = hq.hisq_dslash_shape(dims, prec, -2)
+    shapes = []
+    for shape in range(n):
+        assert hq.hisq_dslash_shape(dims, prec, shape) == shape
+        shapes.append(both())
+    for o in shapes[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(o, shapes[0]))
+    assert not any(np.array_equal(a, b) for a, b in zip(own, shapes[0]))
+    refs = [oracle.dslash(dims, fat, lng, src, p) for p in (0, 1)]
+    for got in (own, shapes[0]):
+        for p in (0, 1):
+            err = oracle.componentwise_error(got[p].astype(np.complex128), refs[p],
+                                             oracle.dslash_scale(dims, fat, lng, src, p))
+            say(f"dslash {dims} prec={prec} parity={p}: componentwise {err:.3e}")
+            assert err <= tol
+        ref = oracle.apply_A(dims, 0.07, fat, lng, src)
+        assert np.linalg.norm(got[2] - ref) / np.linalg.norm(ref) <= tol
+    best, _ = hq.hisq_tune_dslash(L.fat, L.lng, s, torch.empty_like(s), dims, prec, reps=5)
+    assert hq.hisq_dslash_shape(dims, prec) == best
+    tuned = both()
+    assert any(all(np.array_equal(a, b) for a, b in zip(tuned, o)) for o in (own, shapes[0]))
+    for bad in (n, -3):
+        with pytest.raises(hq.HisqError):
+            hq.hisq_dslash_shape(dims, prec, bad)
