@@ -245,7 +245,9 @@ int hisq_dot_noalloc(const void *x, const void *y, long long n, int prec, double
  * the shape is used only if it is faster, and a shape set before no longer
  * counts.
  *
- * The plain CG's fused kernels take the tile order of the chosen shape; for
+ * The plain CG's fused kernels take the tile order of the chosen shape (on
+ * lattices of at most 1280 tiles the CG has kernels of its own, without an
+ * order, unless hisq_dslash_shape has set a shape with a blocked one); for
  * HISQ_F64 a shape with a blocked tile order is chosen only when it is more
  * than 3 % faster than the fastest plain-order shape (the blocked orders slow
  * the CG solve down although the bare Dslash times them close to the plain

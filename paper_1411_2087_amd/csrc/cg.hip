@@ -863,6 +863,10 @@ static Geom cg_geom(const Geom &g, int prec)
     return c;
 }
 
+// A blocked order that a caller set keeps a solve on small lattices in the
+// kernels that have an order, which SplitIter's have not.
+static bool order_was_set(const Geom &c, int prec) { return c.oP && dslash_form(c, prec) == DslashForm::set; }
+
 static void finish_stats(hisq_cg_stats &stats, const CGState *hs, int status, int restarts, double bytes,
                          std::chrono::steady_clock::time_point t0)
 {
@@ -969,7 +973,7 @@ int cg_plain(double mass, double tol, const void *fat, const void *lng, const vo
     if (o.use_graph != 2) {
         char *scratch = (char *)(st + 1);
         const size_t bytes = (size_t)((char *)r - scratch);
-        sp.set(g, PH::prec, st, scratch, bytes);
+        if (!order_was_set(gc, PH::prec)) sp.set(g, PH::prec, st, scratch, bytes);
         if (!sp.on) fo.set(L, PH::prec, scratch, bytes);
     }
     IterTimer tm;
@@ -1072,7 +1076,7 @@ int cg_mixed(double mass, double tol, const void *fat, const void *lng, const vo
 
     const dim3 gb(L.nbl), bb(BL_NT);
     SplitIter sp;  // its scratch: t64, which only the reliable update uses
-    sp.set(g, PS::prec, st, t64, v64);
+    if (!order_was_set(gc, PS::prec)) sp.set(g, PS::prec, st, t64, v64);
     FoldIter fo;
     if (!sp.on) fo.set(L, PS::prec, t64, v64);
     auto settle = [&](hipStream_t q) {

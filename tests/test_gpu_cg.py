@@ -216,3 +216,29 @@ def test_cg_folded_line(hq, dims, mode):
     assert st["rc"] == 0 and tr <= CG_TOL and st["fallback_used"] == 0
     y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, check_every=7)
     assert s2["iters"] == st["iters"] and np.array_equal(x, y)
+
+
+# every kernel form that a blocked order can meet: in place of the small lattices' own kernels (384 tiles; 960, three
+# to a plane), the folded finalisers beyond them (1536), the one-workgroup finalisers of the largest (3456 in FP64, 8704)
+@pytest.mark.parametrize("dims,modes", [((16, 16, 12, 16), (0, 1, 4, 6)), ((16, 24, 20, 16), (0, 6)),
+                                        ((16, 16, 16, 48), (0, 1, 4, 6)), ((16, 24, 32, 36), (0, 4)),
+                                        ((32, 32, 32, 34), (1,))], ids=lambda v: "x".join(map(str, v)))
+def test_cg_takes_the_blocked_order_that_is_set(hq, dims, modes):
+    """Set shape 8 (blocked order) against set shape 6 (the same kernel in plain order): the same solution to tol, and
+    with FP64 vectors other last bits, from the other order of the partial sums (FP32 iterations round alpha and beta
+    to FP32, where that difference is lost)."""
+    mass = 0.2
+    fat, lng = fields(dims, synth.gauge_seed(16))
+    b = synth.source(dims, synth.source_seed(16))
+    for mode in modes:
+        prec = {0: hq.HISQ_F64, 1: hq.HISQ_F32, 4: hq.HISQ_F64C, 6: hq.HISQ_I16SC}[mode]
+        got = {}
+        for shape in (6, 8):
+            hq.hisq_dslash_shape(dims, prec, shape)
+            got[shape] = _solve(hq, dims, fat, lng, b, mass, mode)
+        (x0, s0), (x1, s1) = got[6], got[8]
+        tr = oracle.true_residual(dims, mass, fat, lng, b, x1)
+        say(f"cg set order {dims} mode={mode}: iters {s1['iters']} (plain order {s0['iters']}), resid={tr:.3e}")
+        assert s1["rc"] == 0 and tr <= CG_TOL and s1["fallback_used"] == 0
+        assert abs(s1["iters"] - s0["iters"]) <= 3
+        assert mode not in (0, 4) or not np.array_equal(x0, x1)
