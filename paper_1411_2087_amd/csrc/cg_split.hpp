@@ -274,15 +274,15 @@ struct SplitIter {
                          void *x, int mode) const
     {
         using R = typename P::real;
-        const bool keep = links_stay_cached(g, P::prec);
-        if (fuse) return keep ? launch<P, true, true>(q, g, fat, lng, r, p, t, x, mode)
-                              : launch<P, false, true>(q, g, fat, lng, r, p, t, x, mode);
+        if (fuse) return launch<P, true, true>(q, g, fat, lng, r, p, t, x, mode);
         const long long n16 = (long long)g.Vh * 6 * sizeof(R) / 16;  // Vh is a multiple of 8
         hipLaunchKernelGGL(k_cgs_p<P>, dim3((unsigned)((n16 + 4 * SPLIT_NT - 1) / (4 * SPLIT_NT))), dim3(SPLIT_NT), 0,
                            q, (float4 *)p, (const float4 *)r, n16, (const double *)part_rr, g.ntiles,
                            (const CGState *)s0, s1, mode);
-        return keep ? launch<P, true, false>(q, g, fat, lng, r, p, t, x, mode)
-                    : launch<P, false, false>(q, g, fat, lng, r, p, t, x, mode);
+        // only FP64 links leave the cache below the line, from 869 tiles (1042 with two rows)
+        if constexpr (P::prec == HISQ_F64 || P::prec == HISQ_F64C)
+            if (!links_stay_cached(g, P::prec)) return launch<P, false, false>(q, g, fat, lng, r, p, t, x, mode);
+        return launch<P, true, false>(q, g, fat, lng, r, p, t, x, mode);
     }
     template <class P, bool KEEP, bool FUSE>
     hipError_t launch(hipStream_t q, const Geom &g, const void *fat, const void *lng, void *r, void *p, void *t,

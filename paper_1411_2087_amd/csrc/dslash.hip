@@ -170,7 +170,9 @@ static void launch_split(const Geom &g, const void *fat, const void *lng, const 
                          int gate = GATE_ALWAYS)
 {
     using R = typename P::real;
-    auto k = links_stay_cached(g, P::prec) ? k_dslash_split<P, true, XM> : k_dslash_split<P, false, XM>;
+    auto k = k_dslash_split<P, true, XM>;
+    if constexpr (P::prec == HISQ_F64C)  // the one whose links leave the cache below its line, from 1042 tiles
+        if (!links_stay_cached(g, P::prec)) k = k_dslash_split<P, false, XM>;
     hipLaunchKernelGGL(k, dim3(xcd_grid(g.ntiles)), dim3(SPLIT_NT), 0, s, g, (const char *)fat, (const char *)lng,
                        (const typename P::cvec *)src, (const R *)x, (R *)dst, m4, parity, flags, gate);
 }

@@ -356,13 +356,12 @@ __global__ __launch_bounds__(SPLIT_NT) void k_fs_p(double2 *__restrict__ p, cons
 }
 
 // t = D_oe p ; partials of <p, A p>
-template <bool KEEP>
 __global__ __launch_bounds__(SPLIT_NT) void k_fs_Dp(Geom g, const char *__restrict__ fat,
                                                     const char *__restrict__ lng, const double *__restrict__ p,
                                                     double *__restrict__ t, double *__restrict__ part_pap,
                                                     const FState *__restrict__ s2)
 {
-    using T = SplitTerms<PF64, KEEP>;
+    using T = SplitTerms<PF64, true>;  // up to 768 tiles FP64 links stay in the last-level cache
     __shared__ __align__(16) double red[SPLIT * TILE_REALS];
     __shared__ double ldp[SPLIT];
     if (s2->flags.done) return;
@@ -398,14 +397,13 @@ __global__ __launch_bounds__(SPLIT_NT) void k_fs_Dp(Geom g, const char *__restri
 
 // A p = m4 p - D_eo t in registers ; x += alpha p ; r_prev = r ; r -= alpha A p ;
 // r32 = float(r) ; partials of |r|^2.  alpha from the partials of k_fs_Dp.
-template <bool KEEP>
 __global__ __launch_bounds__(SPLIT_NT) HISQ_WAVES(4) void k_fs_upd(
     Geom g, const char *__restrict__ fat, const char *__restrict__ lng, const double2 *__restrict__ t,
     const double *__restrict__ p, double *__restrict__ x, double *__restrict__ r, double *__restrict__ rp,
     float *__restrict__ r32, const double *__restrict__ part_pap, double *__restrict__ part_rr,
     const FState *__restrict__ s2, FState *__restrict__ s0)
 {
-    using T = SplitTerms<PF64, KEEP>;
+    using T = SplitTerms<PF64, true>;  // up to 768 tiles FP64 links stay in the last-level cache
     __shared__ __align__(16) double red[SPLIT * TILE_REALS];
     __shared__ double lds[SPLIT], ldp[SPLIT];
     const int tile = xcd_block(blockIdx.x, gridDim.x);
@@ -580,7 +578,6 @@ static int fcg_impl(double mass, double tol, const void *fat, const void *lng, c
     const size_t head = (sizeof(FState) + 63) & ~(size_t)63;
     const bool split = split_tiles(g, HISQ_F64) &&
                        2 * head + (2 * (size_t)g.ntiles + 2 * (size_t)nz) * sizeof(double) <= v64;
-    const bool keep = links_stay_cached(g, HISQ_F64);
     FState *s1 = (FState *)z, *s2 = (FState *)((char *)z + head);
     double *part_pap = (double *)((char *)z + 2 * head), *part_rr = part_pap + g.ntiles, *part_z = part_rr + g.ntiles;
     auto split_iter = [&](hipStream_t q) -> hipError_t {
@@ -588,11 +585,9 @@ static int fcg_impl(double mass, double tol, const void *fat, const void *lng, c
         hipLaunchKernelGGL(k_fs_z, gv, nt, 0, q, z32, (const double2 *)r, (const double2 *)rp, n,
                            (const double *)part_rr, g.ntiles, part_z, (const FState *)st, s1);
         hipLaunchKernelGGL(k_fs_p, gv, nt, 0, q, pv, z32, n, (const double *)part_z, nz, (const FState *)s1, s2);
-        auto dp = keep ? k_fs_Dp<true> : k_fs_Dp<false>;
-        hipLaunchKernelGGL(dp, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double *)pv, (double *)t,
-                           part_pap, (const FState *)s2);
-        auto upd = keep ? k_fs_upd<true> : k_fs_upd<false>;
-        hipLaunchKernelGGL(upd, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double2 *)t,
+        hipLaunchKernelGGL(k_fs_Dp, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double *)pv,
+                           (double *)t, part_pap, (const FState *)s2);
+        hipLaunchKernelGGL(k_fs_upd, gt, nt, 0, q, g, (const char *)fat, (const char *)lng, (const double2 *)t,
                            (const double *)pv, (double *)x, (double *)r, (double *)rp, (float *)r32,
                            (const double *)part_pap, part_rr, (const FState *)s2, st);
         return hipGetLastError();

@@ -242,3 +242,21 @@ def test_cg_takes_the_blocked_order_that_is_set(hq, dims, modes):
         assert s1["rc"] == 0 and tr <= CG_TOL and s1["fallback_used"] == 0
         assert abs(s1["iters"] - s0["iters"]) <= 3
         assert mode not in (0, 4) or not np.array_equal(x0, x1)
+
+
+# links that leave the last-level cache within the small lattices' form: 896 and 1024 tiles (FP64 only), the ragged 1048,
+# 1088, the last that its scratch holds in FP64, and the ragged 1094 beyond
+@pytest.mark.parametrize("mode", [0, 4])
+@pytest.mark.parametrize("dims", [(16, 16, 16, 28), (16, 16, 16, 32), (14, 14, 18, 38), (16, 16, 16, 34),
+                                  (18, 18, 18, 24)], ids=lambda d: "x".join(map(str, d)))
+def test_cg_forms_beyond_the_cache(hq, dims, mode):
+    mass = 0.2
+    fat, lng = fields(dims, synth.gauge_seed(17))
+    b = synth.source(dims, synth.source_seed(17))
+    x, st = _solve(hq, dims, fat, lng, b, mass, mode)
+    tr = oracle.true_residual(dims, mass, fat, lng, b, x)
+    say(f"cg beyond the cache {dims} mode={mode}: iters={st['iters']} oracle_resid={tr:.3e}")
+    assert st["rc"] == 0 and tr <= CG_TOL and st["fallback_used"] == 0
+    for kw in (dict(use_graph=0), dict(check_every=7)):
+        y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, **kw)
+        assert s2["iters"] == st["iters"] and np.array_equal(x, y)
