@@ -14,8 +14,8 @@
 //   k_cgs_upd  every workgroup sums those (alpha), A p = 4 m^2 p_new - D_eo t
 //              in registers, p = p_new, x += alpha p, r -= alpha A p, and
 //              the |r|^2 partial of its tile.
-// On up to 1280 tiles the direction update is a kernel of its own again
-// (k_cgs_p, which then finishes the previous iteration), see SplitIter.
+// Beyond 512 tiles the direction update is a kernel of its own again (k_cgs_p,
+// which then finishes the previous iteration), see SplitIter.
 // The sums run while the tile's link and vector loads are in flight.  All
 // workgroups read the same partials in the same order, so they agree to the
 // bit.  The state is read from one copy and written to the other (k_cgs_Dp:
@@ -250,25 +250,41 @@ struct SplitIter {
     void set(const Geom &g, int prec, CGState *st, void *scratch, size_t bytes)
     {
         const size_t n = sizeof(double) * g.ntiles, head = (sizeof(CGState) + 63) & ~(size_t)63;
-        on = g.ntiles <= CG_SPLIT_TILES && head + 2 * n <= bytes;
+        on = split_pays(g, prec) && head + 2 * n <= bytes;
         fuse = g.ntiles <= CG_FUSE_TILES;
         s0 = st;
         s1 = (CGState *)scratch;
         part_pap = (double *)((char *)scratch + head);
         part_rr = part_pap + g.ntiles;
     }
-    // Microseconds per iteration with the five kernels of the large lattices,
-    // the three and the two of the split form (FP64 links; FP32 links):
-    //   8^4 (32 tiles)         41.2 14.3 11.8;   39.8 14.8 11.6
-    //   16^4 (512)             56.9 36.3 36.1;   45.2 27.8 25.2
-    //   16^3 x 32 (1024)       70.0 68.7 72.4;   50.7 41.3 42.0
-    //   20^4 (1250)                              57.9 45.7 47.3
-    //   24^4 (2592)                              97.4 95.8  105
-    //   28^4 (4802)                               162  171  196
-    // Gathering r and p instead of p_new costs bandwidth where the launch it
-    // saves no longer counts, and the sums of all tiles' partials in every
-    // workgroup grow with the square of the lattice.
-    static constexpr int CG_FUSE_TILES = 768, CG_SPLIT_TILES = 1280;
+    // Milliseconds per solve (mass 0.08, tol 1e-10) with these two kernels,
+    // these three, and FoldIter's three:
+    //   tiles   FP64              FP64 two rows     FP32              FP32 two rows     16-bit two rows
+    //    512    17.5 17.1 24.7    15.8 15.6 24.8    12.8 12.9 19.7    11.9 12.2 17.9    13.6 13.9 17.8
+    //    640    21.5 19.8 25.6    19.5 18.2 25.5    15.2 14.3 20.0    14.2 13.4 18.3    14.9 14.5 18.1
+    //    864    29.4 26.7 28.1    25.1 22.8 27.8    19.1 16.9 21.5    17.7 15.8 19.6    16.9 15.8 18.8
+    //    896    32.0 29.4 28.2    25.0 22.4 27.5    18.8 16.6 20.8    17.4 15.2 19.1    16.9 15.9 18.9
+    //   1024    35.0 32.8 31.0    27.5 25.2 29.2    21.2 18.9 21.6    19.4 17.1 20.7    18.4 17.2 20.1
+    //   1088    37.2 35.4 46.0    33.9 31.9 41.0    21.5 19.6 24.4    20.0 17.8 23.5    20.6 19.3 24.4
+    //   1280                                        23.7 21.4 25.9    21.6 19.3 24.6    21.8 20.1 25.5
+    // Two kernels gather r and p instead of p_new, which costs bandwidth where
+    // the launch they save no longer counts.  FP64 links leave the last-level
+    // cache between 864 and 896 tiles (links_stay_cached), and the 8 streams
+    // per tile then lose to FoldIter, until its workgroups of four tiles are
+    // more than the 256 CUs.  The FP64 forms end at 1088 tiles because the
+    // partials lie in the gaps of the plain workspace, which hold no more; the
+    // mixed ones' scratch is larger.  The sums of all tiles' partials in every
+    // workgroup grow with the square of the lattice, but 16-bit links still
+    // gain at 2592 tiles (33.6 against 37.5): their line could be higher.
+    static constexpr int CG_FUSE_TILES = 512;
+    static bool split_pays(const Geom &g, int prec)
+    {
+        switch (prec) {
+        case HISQ_F64: return g.ntiles <= 1088 && (g.ntiles > 1024 || links_stay_cached(g, prec));
+        case HISQ_F64C: return g.ntiles <= 1088;
+        default: return g.ntiles <= 1280;
+        }
+    }
     template <class P>
     hipError_t iteration(hipStream_t q, const Geom &g, const void *fat, const void *lng, void *r, void *p, void *t,
                          void *x, int mode) const

@@ -260,3 +260,20 @@ def test_cg_forms_beyond_the_cache(hq, dims, mode):
     for kw in (dict(use_graph=0), dict(check_every=7)):
         y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, **kw)
         assert s2["iters"] == st["iters"] and np.array_equal(x, y)
+
+
+# the lines between the kernel forms: the last lattice with two kernels per iteration and the first with three; and the
+# first in FP64 whose links leave the cache, where folded finalisers take over up to 1024 tiles
+@pytest.mark.parametrize("dims,modes", [((16, 16, 16, 16), (0, 1, 6)), ((14, 14, 14, 24), (0, 1, 6)),
+                                        ((14, 14, 16, 36), (0, 4))], ids=lambda v: "x".join(map(str, v)))
+def test_cg_lines_between_forms(hq, dims, modes):
+    mass = 0.2
+    fat, lng = fields(dims, synth.gauge_seed(18))
+    b = synth.source(dims, synth.source_seed(18))
+    for mode in modes:
+        x, st = _solve(hq, dims, fat, lng, b, mass, mode)
+        tr = oracle.true_residual(dims, mass, fat, lng, b, x)
+        say(f"cg lines {dims} mode={mode}: iters={st['iters']} oracle_resid={tr:.3e}")
+        assert st["rc"] == 0 and tr <= CG_TOL and st["fallback_used"] == 0
+        y, s2 = _solve(hq, dims, fat, lng, b, mass, mode, check_every=7)
+        assert s2["iters"] == st["iters"] and np.array_equal(x, y)
