@@ -134,17 +134,32 @@ void set_dslash_choice(const Geom &g, int prec, int shape, DslashForm form)
     count_forms_locked();
 }
 
-// Untuned default per precision: two terms unrolled at 5 waves per SIMD for
-// the FP64 forms, every term in flight for FP32 links, four terms at 4 waves
-// for 16-bit ones.  Microseconds on 32x40x24x96 (one term at 8 waves, this):
-// F32 316, 298; F32C 272, 262; F16S 190, 177; I16S 189, 175; I16SC 172, 163.
-// FP64 with more workgroups of four tiles than CUs, but not twice as many,
-// takes workgroups of one tile, which level the last round (20^4: 41.5, 32.2).
+// Untuned default.  Shape 2 has workgroups of one tile; 3 and 4 have every term
+// and four terms in flight, 10 two, 0 one, all with workgroups of four tiles,
+// which leave a round of the 1024 tiles that the CUs take nearly empty just
+// beyond each multiple of 1024.  Microseconds (three states in turn, so that
+// nothing is left in a cache from the call before), shapes as headed:
+//   tiles         1337       1625       2048       2808       3072       3822       4608       5120       5440       7168       13122
+//   F64   10, 2   44.2 36.6  47.8 42.7  52.6 51.1  74.4 73.1  79.2 80.5  101  98    122  119   130  134   139  139   180  185   341  353
+//   F32   3, 2    21.5 18.0  23.4 20.9  26.7 26.0  37.8 36.7  39.8 40.6  49.3 49.6  59.8 59.0  65.3 67.0  70.4 70.5  89.7 93.2  171  182
+//   F32C  3, 2    19.7 17.3  21.1 19.0  23.5 21.7  33.1 30.9  34.0 33.9  43.7 43.4  53.1 51.7  54.9 56.5  62.0 61.5  77.4 81.0  148  154
+//   I16S  4, 2                                     25.2 21.9  26.8 23.7  31.3 29.6  37.7 37.5  39.4 40.7  50.3 44.3  58.3 56.7  101  109
+//   I16SC 4, 2                                     22.1 20.5  22.6 21.9  28.5 27.5  35.3 35.0  39.0 38.2  40.9 41.4  50.7 52.1  95.5 99.8
+// (F16S within 6 % of I16S.)  Shape 0 is slower than the one chosen but for
+// 1-2 % at single sizes (F32C 3021: 33.7 against 34.2).  Why four terms in
+// flight lose to one above 5120 tiles with 16-bit links, 45.3 against 50.3 at
+// 5440, was not found.  F64C takes two terms at every size (2: 1.5 times as slow).
 static int default_dslash_shape(const Geom &g, int prec)
 {
-    if (prec == HISQ_F64 && g.ntiles > 1024 && g.ntiles <= 1536) return 2;
-    if (prec == HISQ_F64 || prec == HISQ_F64C) return 10;
-    return (prec == HISQ_F32 || prec == HISQ_F32C) ? 3 : 4;
+    const int n = g.ntiles;
+    switch (prec) {
+    case HISQ_F64: return n > 1024 && n <= 2816 ? 2 : 10;
+    case HISQ_F64C: return 10;
+    case HISQ_F32: return n <= 2816 ? 2 : 3;
+    case HISQ_F32C: return n <= 4608 ? 2 : 3;
+    case HISQ_I16SC: return n <= 5120 ? 2 : 4;
+    default: return n <= 4608 || (n > 5120 && n <= 7168) ? 2 : 4;
+    }
 }
 
 int tuned_dslash_shape(const Geom &g, int prec)
