@@ -1094,20 +1094,29 @@ static const MShape MSHAPES[N_MSHAPES] = { { 1, 256, 0, 0 }, { 2, 256, 0, 0 }, {
                                            { 4, 256, 0, 1 }, { 4, 256, 1, 1 }, { 2, 256, 1, 1 }, { 4, 256, 1, 3 },
                                            { 2, 256, 1, 3 }, { 4, 256, 1, 4 }, { 2, 256, 1, 4 }, { 4, 256, 1, 5 } };
 
-// Untuned choice, from the times of every shape (us; one RHS group per site
-// and 256 threads, this): N = 1 32^4 111, 102; N = 2 16^4 18.0, 17.4; N = 4
-// 8^4 15.1, 9.9, 16^4 21.8, 17.7, 32^4 147, 140; N = 8 16^4 31.7, 19.5, 24^4
-// 85, 76, 32^4 231, 214; N = 16 8^4 47.2, 15.5, 16^4 58, 27, 32^4 476, 382.
-// Four threads per site (2: loads as they are needed; 4: issued a direction
-// ahead) fill the chip on few tiles, and keep N = 16 in registers.
+// Untuned choice, from the times of the shapes on 53 lattices (us, three states
+// in turn; shape 0, one RHS group per site and 256 threads, then others):
+//   tiles           32        512       960       1088      1664      2160      3072*     4608      5120      8192
+//   N = 1   0, 3    10.8 9.6  21.2 20.0 24.6 24.6 28.8 26.0 31.4 30.9 36.2 34.7 41.9 41.5 66.7 68.0 69.4 72.0 111 106
+//   N = 2   0, 3    12.4 12.1 20.5 20.3 21.8 22.5 24.7 23.4 27.4 27.8 41.9 35.4 45.3 45.9 70.7 67.7 74.2 74.7 115 120
+//   N = 4   0, 1    16.3 12.7 24.1 20.6 26.3 23.1 32.9 27.9 36.9 39.9 53.5 47.2 57.5 58.5 90.1 85.3 93.1 93.9 148 151
+//              5    14.0      21.4      26.1      29.2      36.6      52.7      59.5      86.4      93.4      143
+//   N = 8   0, 2    25.1 12.9 33.4 21.8 36.6 33.8 49.6 41.3 54.1 53.7 83.2 67.3           138 133   148 152   238 241
+//              4    14.0      24.2      30.8      44.8      53.0      69.8                125       140       222
+//   N = 16  0, 4    48.8 19.2 60.0 28.7 64.3 50.0 115 57.8  120 79.8  176 106             298 214   304 236   475 382
+// (* 3024.)  Four threads per site (2: loads as they are needed; 4: issued a
+// direction ahead) fill the chip on few tiles, and keep N = 16 in registers.
+// The 256 CUs take workgroups of four tiles in rounds of 1024; where the last
+// round would be less than half full, N = 2 gains from workgroups of two.
 static int default_mshape(const Geom &g, int N)
 {
+    const int n = g.ntiles;
     switch (N) {
-    case 1: return 3;
-    case 2: return g.ntiles <= 2048 ? 3 : 0;
-    case 4: return g.ntiles <= 64 ? 2 : g.ntiles <= 4096 ? 1 : 5;
-    case 8: return g.ntiles <= 1280 ? 2 : 4;
-    default: return g.ntiles <= 64 ? 2 : 4;
+    case 1: return n > 4096 && n <= 5120 ? 0 : 3;
+    case 2: return n <= 512 || (n > 1024 && (n - 1) % 1024 < 512) ? 3 : 0;
+    case 4: return n <= 64 ? 2 : n <= 1536 || (n > 2048 && n <= 3072) ? 1 : 5;
+    case 8: return n <= 1280 ? 2 : 4;
+    default: return n <= 64 ? 2 : 4;
     }
 }
 template <class PS> static int mshape_for(const Geom &g, int N)

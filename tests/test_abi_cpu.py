@@ -241,3 +241,14 @@ def test_default_dslash_shapes_are_the_measured_ones(dims, shapes):
     is not slower (16-bit links at 5376 tiles: 43.7 us with shape 2, 47.5-50.0 with 4, 45 with 0)."""
     import paper_1411_2087_amd as hq
     assert tuple(None if s is None else hq.hisq_dslash_shape(dims, p) for p, s in enumerate(shapes)) == shapes
+
+
+@pytest.mark.parametrize("dims,shapes", [((8, 8, 8, 8), (3, 3, 2)), ((16, 16, 16, 20), (3, 0, 1)),
+                                         ((16, 16, 16, 34), (3, 3, 1)), ((22, 22, 22, 20), (3, 0, 5)),
+                                         ((24, 24, 24, 22), (3, 3, 1)), ((24, 24, 28, 30), (3, 0, 5)),
+                                         ((20, 32, 32, 32), (0, 0, 5)), ((32, 32, 32, 32), (3, 0, 5))],
+                         ids=lambda v: "x".join(map(str, v)) if len(v) == 4 else "")
+def test_default_multi_shapes_are_the_measured_ones(dims, shapes):
+    """N = 1, 2, 4 on lattices where the default has been timed against shape 0 and is not slower."""
+    import paper_1411_2087_amd as hq
+    assert tuple(hq.hisq_multi_shape(dims, n) for n in (1, 2, 4)) == shapes
