@@ -170,7 +170,9 @@ typedef struct {
                                microseconds of the iteration's three main kernels, timed with
                                HIP events on the solve's stream: [0] t = D_oe p with the |t|^2
                                partials, [1] the parity-0 Dslash with A p in registers and the
-                               x, r updates, [2] p = r + beta p with |p|^2; 0 otherwise */
+                               x, r updates, [2] p = r + beta p with |p|^2; 0 otherwise.
+                               These are the kernels of the largest lattices on every lattice;
+                               with use_graph 0 or 1 a smaller one runs fewer, fused kernels */
 } hisq_cg_stats;
 
 /* Library version string. */

@@ -38,9 +38,107 @@ struct CGState {
     int last_upd;    // iteration of the last reliable update
     int first_gap;   // iterations from the start to the first reliable update
     int poor;        // consecutive reliable updates that did not halve |r|
-    int pending;     // cg_split.hpp: the last iteration's |r|^2 partials are not in the state yet
+    int pending;     // the last iteration's |r|^2 partials are not in the state yet
 };
 
+// What a finished reduction, of value v, does to the state.
+enum {
+    FIN_BB = 0,           // bb = v ; stop2 = tol2 * bb
+    FIN_PAP = 1,          // pAp = v ; alpha or breakdown
+    FIN_UPD_PLAIN = 2,    // rr_new = v ; iter++ ; converged? ; beta ; rr
+    FIN_UPD_MIXED = 3,    // as above, deciding reliable updates
+    FIN_INIT_PLAIN = 4,   // rr = rr_true = v ; done = v <= stop2
+    FIN_TRUE = 5,         // rr_true = v
+    FIN_RELIABLE = 6,     // rr_true = v ; beta = v / rr ; rr = maxrr = v ; reliable = 0 ; done?
+    FIN_INIT_MIXED = 7,   // rr = maxrr = rr_true = v ; done = v <= stop2
+};
+
+__device__ __forceinline__ void finalize(CGState *st, int mode, double v)
+{
+    switch (mode) {
+    case FIN_BB:
+        st->bb = v;
+        st->stop2 = st->tol2 * v;
+        break;
+    case FIN_PAP:
+        st->pAp = v;
+        if (!(v > 0.0) || !isfinite(v)) {
+            st->flags.done = CG_BREAKDOWN;
+        } else {
+            st->alpha = st->rr / v;
+        }
+        break;
+    case FIN_UPD_PLAIN:
+        st->rr_new = v;
+        st->iter += 1;
+        if (!isfinite(v)) {
+            st->flags.done = CG_BREAKDOWN;
+        } else if (v <= st->stop2) {
+            st->flags.done = CG_CONVERGED;
+            st->rr = v;
+        } else {
+            st->beta = v / st->rr;
+            st->rr = v;
+        }
+        break;
+    case FIN_UPD_MIXED:
+        st->rr_new = v;
+        st->iter += 1;
+        if (!isfinite(v)) {
+            st->flags.done = CG_BREAKDOWN;
+        } else if (v <= st->stop2 || v < st->delta2 * st->maxrr) {
+            st->flags.reliable = 1;
+        } else {
+            st->maxrr = fmax(st->maxrr, v);
+            st->beta = v / st->rr;
+            st->rr = v;
+            // the inner solve has gone ten times as long as its first cycle without a reliable update
+            if (st->first_gap > 0 && st->iter - st->last_upd > 10 * st->first_gap + 1000) st->flags.done = CG_STALLED;
+        }
+        break;
+    case FIN_INIT_PLAIN:
+        st->beta = 0.0;  // the first direction is p = r
+        st->rr = v;
+        st->rr_true = v;
+        st->flags.done = (v <= st->stop2) ? CG_CONVERGED : 0;
+        break;
+    case FIN_TRUE:
+        st->rr_true = v;
+        break;
+    case FIN_RELIABLE: {
+        const int gap = st->iter - st->last_upd;
+        if (st->first_gap == 0) st->first_gap = gap > 0 ? gap : 1;
+        // poor: the true residual fell by less than sqrt(delta) since the last
+        // update (an update fires after a fall by delta in the iterated residual),
+        // or did not halve when delta is small
+        st->poor = (v > fmax(0.25, sqrt(st->delta2)) * st->rr_upd) ? st->poor + 1 : 0;
+        st->rr_upd = v;
+        st->last_upd = st->iter;
+        st->rr_true = v;
+        st->nupdates += 1;
+        st->beta = v / st->rr;
+        st->rr = v;
+        st->maxrr = v;
+        st->flags.reliable = 0;
+        if (!isfinite(v)) st->flags.done = CG_BREAKDOWN;
+        else if (v <= st->stop2) st->flags.done = CG_CONVERGED;
+        else if (st->poor >= 2) st->flags.done = CG_STALLED;  // the inner operator is too far from A
+        break;
+    }
+    case FIN_INIT_MIXED:
+        st->beta = 0.0;
+        st->rr = v;
+        st->maxrr = v;
+        st->rr_true = v;
+        st->rr_upd = v;
+        st->last_upd = 0;
+        st->first_gap = 0;
+        st->poor = 0;
+        st->flags.reliable = 0;
+        st->flags.done = (v <= st->stop2) ? CG_CONVERGED : 0;
+        break;
+    }
+}
 
 // Scratch of the standalone dot product: the per-workgroup partials of the
 // first stage (at most BLAS_MAX_BLOCKS workgroups, striding over the vectors)

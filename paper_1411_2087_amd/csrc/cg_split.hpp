@@ -1,5 +1,5 @@
 // The CG iteration on small lattices: two kernels (three on the larger of
-// them), one 64-site tile per workgroup (SplitTerms).  Included by cg.hip.
+// them), one 64-site tile per workgroup (SplitTerms).
 //
 // On a few hundred tiles an iteration is launches and latency, not bytes: at
 // 8^4 the five kernels of the large-lattice iteration (two Dslashes with their

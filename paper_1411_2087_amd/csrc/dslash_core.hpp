@@ -125,11 +125,12 @@ __device__ __forceinline__ void dslash_site(const Geom &g, const char *__restric
 // one-link and the three-link term of direction q, all its loads in flight at
 // once, and the 8 partial sums meet in LDS, where they are added in the order
 // of q.  Bound by latency (launch, one round trip to memory, one barrier).
-// Microseconds per Dslash, one wavefront per tile -> split (4 and 16
-// wavefronts per tile are within 5 %, or slower):
-//   FP64   8^4 16.2 -> 3.6, 16^4 20.6 -> 13.0, 20^4 42.1 -> 35.4
-//   FP32   8^4 12.5 -> 2.9, 16^4 14.2 -> 7.7, 20^4 21.4 -> 15.6, 28^4 66.2 -> 63.6
-//   I16SC  8^4 12.7 -> 3.0, 16^4 13.7 -> 5.7, 20^4 16.5 -> 9.5, 28^4 39.0 -> 35.1
+// Microseconds per Dslash, the default shape at 8^4 and the fastest shape at
+// the others -> split (4 and 16 wavefronts per tile are within 5 %, or slower):
+//   FP64   8^4 16.2 -> 3.6, 16^4 19.6 -> 13.0
+//   FP32   8^4 12.5 -> 2.9, 16^4 11.6 -> 7.7, 20^4 17.5 -> 15.6
+//   I16SC  8^4 12.7 -> 3.0, 16^4 9.6 -> 5.7, 20^4 14.7 -> 9.5, 24^4 20.1 -> 17.0
+// split_tiles has both sides of the lines.
 // KEEP: link loads through the caches (links_stay_cached).
 constexpr int SPLIT = 8;
 constexpr int SPLIT_NT = SPLIT * TILE;
@@ -185,22 +186,6 @@ template <class P, bool KEEP> struct SplitTerms {
         return s;
     }
 };
-// Algorithmic bytes per site of the byte model of every solver's bytes_moved:
-// the 16 link matrices of one Dslash in precision `prec` (a two-row long
-// matrix is 96, 48 or 28 bytes) and one colour vector of its vector type.
-inline double link_bytes_site(int prec)
-{
-    switch (prec) {
-    case HISQ_F64: return 16 * 144.0;
-    case HISQ_F32: return 16 * 72.0;
-    case HISQ_F16S:
-    case HISQ_I16S: return 16 * 40.0;
-    case HISQ_F64C: return 8 * 144.0 + 8 * 96.0;
-    case HISQ_F32C: return 8 * 72.0 + 8 * 48.0;
-    default: return 8 * 40.0 + 8 * 28.0;  // HISQ_I16SC
-    }
-}
-inline double vec_bytes(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 48.0 : 24.0; }
 
 // Whether a lattice takes the split form in this precision where no shape was
 // asked for (dslash_form), and whether its packed links stay in the last-level

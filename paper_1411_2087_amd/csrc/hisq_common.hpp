@@ -82,6 +82,23 @@ __device__ __forceinline__ int tile_of(const Geom &g, int k)
 size_t dir_block_bytes(int prec);
 size_t packed_field_bytes(const Geom &g, int prec);
 
+// Algorithmic bytes per site of the byte model of every solver's bytes_moved:
+// the 16 link matrices of one Dslash in precision `prec` (a two-row long
+// matrix is 96, 48 or 28 bytes) and one colour vector of its vector type.
+inline double link_bytes_site(int prec)
+{
+    switch (prec) {
+    case HISQ_F64: return 16 * 144.0;
+    case HISQ_F32: return 16 * 72.0;
+    case HISQ_F16S:
+    case HISQ_I16S: return 16 * 40.0;
+    case HISQ_F64C: return 8 * 144.0 + 8 * 96.0;
+    case HISQ_F32C: return 8 * 72.0 + 8 * 48.0;
+    default: return 8 * 40.0 + 8 * 28.0;  // HISQ_I16SC
+    }
+}
+inline double vec_bytes(int prec) { return (prec == HISQ_F64 || prec == HISQ_F64C) ? 48.0 : 24.0; }
+
 __device__ __forceinline__ void site_coords(const Geom &g, int h, int parity, int &x, int &y, int &z, int &t)
 {
     int r = h / g.Lxh;
