@@ -209,8 +209,10 @@ static int tune_dslash_impl(const Geom &g, const void *fat, const void *lng, con
     // order is slower than the plain one (32^4, m = 0.01: 1.80-1.86 s against 1.76 s per solve, the same in
     // three alternating rounds), while the bare Dslash times the orders within 2 % of each other either way.
     // A blocked shape is kept only when it beats the best plain-order shape by more than 3 %.
-    if (P::prec == HISQ_F64 && plain_i >= 0 && DSLASH_SHAPES[best_i].order != 0 && best_us > 0.97 * plain_us)
+    if (P::prec == HISQ_F64 && plain_i >= 0 && DSLASH_SHAPES[best_i].order != 0 && best_us > 0.97 * plain_us) {
         best_i = plain_i;
+        best_us = plain_us;
+    }
     DslashForm form = DslashForm::rule;
     if (split_tiles(g, P::prec)) {
         const double us = time_launches([&]() { return launch_dslash_tiles<P>(g, fat, lng, src, dst, 1, s); }, reps, s);
