@@ -154,12 +154,18 @@ __device__ __forceinline__ void store_rows(char *tile_base, int d, int lane, con
 // and 1 of every matrix, plus the sign word of each (tile, direction) built
 // with a wavefront ballot; `status` is set when a matrix is not +-SU(3) to
 // 1e-6 (padding lanes are exempt).
+//
+// STAGED = false, on few sites: each lane reads its own matrix after all.  There
+// the barriers and the way through LDS cost more than the lines (both
+// fields, FP32, us, through LDS and read directly: 4^4 7.7, 6.1; 8^4 8.3, 6.7;
+// 10x8x10x8 9.1, 7.9; 8x12x12x12 11.2, 11.1; 12^4 14.9, 16.9; 14^4 21.3, 24.7).
 constexpr int PACK_NT = 256;
-template <int PREC, class ROWS>
+constexpr long long PACK_DIRECT_SITES = 16384;
+template <int PREC, class ROWS, bool STAGED>
 __global__ __launch_bounds__(PACK_NT) void k_pack(Lex l, Geom g, const double2 *__restrict__ canon,
                                                   char *__restrict__ out, int hop, size_t block_bytes, int *status)
 {
-    __shared__ Stage<PACK_NT> st;
+    __shared__ Stage<STAGED ? PACK_NT : 1> st;
     // without ROWS: a status word to clear for the kernel that follows (a fill launch of its own costs more than
     // this kernel on the smallest lattices)
     if constexpr (std::is_void<ROWS>::value)
@@ -168,7 +174,7 @@ __global__ __launch_bounds__(PACK_NT) void k_pack(Lex l, Geom g, const double2 *
     const long long n = (long long)blk * PACK_NT + threadIdx.x;
     if ((long long)blk * PACK_NT >= l.V) return;
     int cs[4] = { 0, 0, 0, 0 };
-    if (n < l.V) lex_coords(l, n, cs);
+    if (STAGED && n < l.V) lex_coords(l, n, cs);
     // this wavefront's tile and parity; its lane's site is canonical site 2 h + bit
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, parity = w & 1, tile = 2 * blk + (w >> 1);
     const int h = tile * TILE + lane;
@@ -183,15 +189,23 @@ __global__ __launch_bounds__(PACK_NT) void k_pack(Lex l, Geom g, const double2 *
     for (int k = blockIdx.y * per; k < (int)(blockIdx.y + 1) * per; ++k) {
         const int mu = k >> 1, d = mu + 4 * (k & 1);
         const bool bwd = d >= 4;
-        long long src = -1;
-        if (n < l.V) src = (long long)mu * l.V + (bwd ? lex_hop(l, n, cs, mu, -hop) : n);
-        stage_in<PACK_NT>(st, canon, src);
+        if constexpr (STAGED) {
+            long long src = -1;
+            if (n < l.V) src = (long long)mu * l.V + (bwd ? lex_hop(l, n, cs, mu, -hop) : n);
+            stage_in<PACK_NT>(st, canon, src);
+        }
         if (tile >= g.ntiles) continue;  // wave-uniform; the barriers are in stage_in
         double m[18];
 #pragma unroll
         for (int e = 0; e < 18; ++e) m[e] = 0.0;
         if (valid) {
-            const double2 *u = st.m + 9 * mine;
+            const double2 *u;
+            if constexpr (STAGED) {
+                u = st.m + 9 * mine;
+            } else {
+                const long long own = 2LL * h + (c[0] & 1);
+                u = canon + 9 * ((long long)mu * l.V + (bwd ? lex_hop(l, own, c, mu, -hop) : own));
+            }
             // backward: -U^dag, entry (a, b) = -conj(U_ba)
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -261,26 +275,34 @@ extern "C" int hisq_pack_links(const void *fat_canon, const void *long_canon, co
     if (!aligned16({fat_canon, long_canon, fat_out, long_out}))
         return fail(HISQ_EINVAL, "hisq_pack_links: device pointers must be 16-byte aligned");
     if (fat_out == long_out) return fail(HISQ_EALIAS, "hisq_pack_links: fat_out and long_out alias");
-    const size_t bb = dir_block_bytes(prec);
-    if (!bb) return fail(HISQ_EINVAL, "hisq_pack_links: unknown precision");
+    if (!dir_block_bytes(prec)) return fail(HISQ_EINVAL, "hisq_pack_links: unknown precision");
     hipStream_t s = (hipStream_t)stream;
     Lex l;
     if (make_lex(dims, l)) return HISQ_EDIMS;
     // where the sites alone do not fill the chip (4 workgroups per CU), the directions are shared out too
     const int nb = (int)((l.V + PACK_NT - 1) / PACK_NT), split = nb >= 1024 ? 1 : nb >= 256 ? 4 : 8;
     const dim3 grid(xcd_grid(nb), split), block(PACK_NT);
-    auto full = [&](auto kernel, const void *in, void *out, int hop, size_t bytes, int *clear = nullptr) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, l, g, (const double2 *)in, (char *)out, hop, bytes, clear);
+    auto launch = [&](auto kernel, const void *in, void *out, int hop, size_t bytes, int *status = nullptr) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, l, g, (const double2 *)in, (char *)out, hop, bytes, status);
+    };
+    const bool staged = l.V > PACK_DIRECT_SITES;
+    auto full = [&](int fp, const void *in, void *out, int hop, int *clear = nullptr) {
+        auto kernel = fp == HISQ_F64    ? (staged ? k_pack<HISQ_F64, void, true> : k_pack<HISQ_F64, void, false>)
+                      : fp == HISQ_F32  ? (staged ? k_pack<HISQ_F32, void, true> : k_pack<HISQ_F32, void, false>)
+                      : fp == HISQ_F16S ? (staged ? k_pack<HISQ_F16S, void, true> : k_pack<HISQ_F16S, void, false>)
+                                        : (staged ? k_pack<HISQ_I16S, void, true> : k_pack<HISQ_I16S, void, false>);
+        launch(kernel, in, out, hop, dir_block_bytes(fp), clear);
     };
     if (prec == HISQ_F64C || prec == HISQ_F32C || prec == HISQ_I16SC) {
         const int fp = prec == HISQ_F64C ? HISQ_F64 : (prec == HISQ_F32C ? HISQ_F32 : HISQ_I16S);
         int *status = reinterpret_cast<int *>((char *)long_out + long_field_bytes(g, prec) - 256);
-        full(fp == HISQ_F64 ? k_pack<HISQ_F64, void> : fp == HISQ_F32 ? k_pack<HISQ_F32, void> : k_pack<HISQ_I16S, void>,
-             fat_canon, fat_out, 1, dir_block_bytes(fp), status);
-        hipLaunchKernelGGL((prec == HISQ_F64C   ? k_pack<HISQ_F64C, PF64R>
-                            : prec == HISQ_F32C ? k_pack<HISQ_F32C, PF32R>
-                                                : k_pack<HISQ_I16SC, PI16R>),
-                           grid, block, 0, s, l, g, (const double2 *)long_canon, (char *)long_out, 3, (size_t)0, status);
+        full(fp, fat_canon, fat_out, 1, status);
+        auto rows = prec == HISQ_F64C
+                        ? (staged ? k_pack<HISQ_F64C, PF64R, true> : k_pack<HISQ_F64C, PF64R, false>)
+                    : prec == HISQ_F32C
+                        ? (staged ? k_pack<HISQ_F32C, PF32R, true> : k_pack<HISQ_F32C, PF32R, false>)
+                        : (staged ? k_pack<HISQ_I16SC, PI16R, true> : k_pack<HISQ_I16SC, PI16R, false>);
+        launch(rows, long_canon, long_out, 3, (size_t)0, status);
         HISQ_HIP(hipGetLastError());
         int h_status = 0;
         HISQ_HIP(hipMemcpyAsync(&h_status, status, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -288,12 +310,8 @@ extern "C" int hisq_pack_links(const void *fat_canon, const void *long_canon, co
         if (h_status) return fail(HISQ_EINVAL, "hisq_pack_links: a long link is not +-SU(3) to 1e-6; use an uncompressed precision");
         return HISQ_OK;
     }
-    auto kernel = prec == HISQ_F64    ? k_pack<HISQ_F64, void>
-                  : prec == HISQ_F32  ? k_pack<HISQ_F32, void>
-                  : prec == HISQ_F16S ? k_pack<HISQ_F16S, void>
-                                      : k_pack<HISQ_I16S, void>;
-    full(kernel, fat_canon, fat_out, 1, bb);
-    full(kernel, long_canon, long_out, 3, bb);
+    full(prec, fat_canon, fat_out, 1);
+    full(prec, long_canon, long_out, 3);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "hisq_pack_links launch");
     return HISQ_OK;

@@ -212,3 +212,46 @@ def test_fat_paths_round_no_more_than_the_staples(hq, coeff):
         rms.append(float(np.sqrt(np.mean(np.abs(out.cpu().numpy() - ref) ** 2))))
     say(f"fat paths {coeff}: rms error {rms[0]:.3e}, staple by staple {rms[1]:.3e}")
     assert rms[0] <= 1.02 * rms[1]
+
+
+# the last lattices whose matrices are read directly (16384 sites) and the first through LDS, one of them ragged
+@pytest.mark.parametrize("dims", [(16, 8, 8, 16), (8, 12, 12, 14), (10, 10, 10, 18), (12, 12, 12, 10)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_pack_agrees_across_its_line(hq, dims):
+    """Every packed form against the FP64 form of the same links, entry by entry: its matrices to its storage's
+    rounding, and its two-row forms' rows and signs exactly in FP64."""
+    import torch
+    fat, lng = synth.links(dims, 37)
+    V = dims[0] * dims[1] * dims[2] * dims[3]
+    nt = (V // 2 + 63) // 64
+    full = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F64)
+    ref = full.lng.cpu().numpy().view(np.complex128).reshape(2, nt, 8, 9, 64)
+    lex = np.arange(V)
+    x = [lex % dims[0], lex // dims[0] % dims[1], lex // (dims[0] * dims[1]) % dims[2], lex // (dims[0] * dims[1] * dims[2])]
+    par, h = sum(x) % 2, lex >> 1
+    for mu in range(4):
+        y = [v.copy() for v in x]
+        y[mu] = (y[mu] - 3) % dims[mu]
+        back = y[0] + dims[0] * (y[1] + dims[1] * (y[2] + dims[2] * y[3]))
+        assert np.array_equal(ref[par, h >> 6, mu, :, h & 63], lng[mu].reshape(V, 9))
+        assert np.array_equal(ref[par, h >> 6, mu + 4, :, h & 63],
+                              -np.conj(np.swapaxes(lng[mu][back], 1, 2)).reshape(V, 9))
+    C = hq.fields.Links.pack(fat, lng, dims, hq.HISQ_F64C)
+    tile = 8 * 6 * 64 * 16 + 64
+    got = C.lng.cpu().numpy()[:2 * nt * tile].reshape(2, nt, tile)
+    rows = np.ascontiguousarray(got[:, :, :-64]).view(np.complex128).reshape(2, nt, 8, 6, 64)
+    assert np.array_equal(rows, ref[:, :, :, :6])
+    m = np.moveaxis(ref, 3, 4).reshape(2, nt, 8, 64, 3, 3)
+    word = ((np.linalg.det(m).real < 0).astype(np.uint64) << np.arange(64, dtype=np.uint64)).sum(-1, dtype=np.uint64)
+    assert np.array_equal(np.ascontiguousarray(got[:, :, -64:]).view(np.uint64), word)
+    src = torch.from_numpy(synth.source(dims, 41).astype(np.complex64)).cuda()
+    want = torch.empty(src.shape, dtype=torch.complex128, device="cuda")
+    hq.dslash_apply(full.fat, full.lng, src.to(torch.complex128), want, 0, dims, hq.HISQ_F64)
+    for prec, tol in ((hq.HISQ_F32, 1e-6), (hq.HISQ_F16S, 5e-3), (hq.HISQ_I16S, 5e-4), (hq.HISQ_F32C, 1e-6),
+                      (hq.HISQ_I16SC, 5e-4)):
+        L = hq.fields.Links.pack(fat, lng, dims, prec)
+        out = torch.empty_like(src)
+        hq.dslash_apply(L.fat, L.lng, src, out, 0, dims, prec)
+        err = float(torch.linalg.vector_norm(out.to(torch.complex128) - want) / torch.linalg.vector_norm(want))
+        say(f"pack {dims} prec={prec}: Dslash differs by {err:.2e}")
+        assert err <= tol
